@@ -11,14 +11,15 @@
 //
 // Deposit.  A move x0 -> x1 shorter than one cell touches at most three
 // nodes per axis, [b, b+2] with b = min(floor x0, floor x1).  Its current is
-// 18 Jx + 18 Jy + 18 Jz edge values on that window.  Particles are kept
-// sorted by cell, so the lanes of a wavefront mostly share a window: lanes
-// with equal windows are summed across the wavefront by recursive halving
-// (64 slots -> one slot per lane).  The two widest exchange rounds use the
-// gfx950 half-wave swaps (v_permlane32_swap, v_permlane16_swap), the four
-// narrow ones DPP lane moves, so no round goes through LDS.  Each lane then
-// issues at most one global float atomic.  Windows still unresolved after a
-// few rounds fall back to per-lane atomics.
+// 18 Jx + 18 Jy + 18 Jz edge values on that window, each a product of one
+// factor per axis.  Particles are kept sorted by cell, so the lanes of a
+// wavefront mostly share a grid row: the sum over the particles of a row is a
+// small matrix product (x factors times transverse factors) and runs on the
+// matrix cores in FP32 (deposit_rows).  Rows with few lanes use per-lane
+// atomics.  The fixed-point deposit sums integers instead: lanes with equal
+// windows by recursive halving (64 slots -> one slot per lane), the two widest
+// exchanges by the gfx950 half-wave swaps (v_permlane32_swap,
+// v_permlane16_swap), the four narrow ones by DPP lane moves.
 #include "pic_internal.hpp"
 
 namespace pic {
@@ -146,17 +147,35 @@ __device__ __forceinline__ float gather_scalar(const float *__restrict__ f, cons
     return v;
 }
 
-// First-order shape on the 3-node window starting at node `base`.
-__device__ __forceinline__ void shapes(float x0, float x1, int base, float S0[3], float dS[3])
+__device__ __forceinline__ float clamp01(float v) { return __builtin_amdgcn_fmed3f(v, 0.f, 1.f); }
+
+// Esirkepov factors of one axis of a move x0 -> x1 on the 3-node window
+// starting at node `base`, with S0, S1 the first-order shapes before and after
+// and dS = S1 - S0: A = (S0 + S1)/2 and D = dS / sqrt(12) per node, and the
+// running sum P of dS per edge.  The transverse weight of two axes is
+//   S0 S0' + (dS S0' + S0 dS')/2 + dS dS'/3 = A A' + D D',
+// and an edge current is P (its own axis) times that of the other two.
+struct AxisF {
+    float A[3], D[3], P[2];
+};
+constexpr float RSQRT12 = 0.28867513459481287f;
+
+__device__ __forceinline__ AxisF axis_factors(float x0, float x1, int base)
 {
     const float r0 = x0 - (float)base, r1 = x1 - (float)base;
+    float dS[3];
+    AxisF f;
 #pragma unroll
     for (int m = 0; m < 3; ++m) {
-        const float s0 = fmaxf(0.f, 1.f - fabsf(r0 - (float)m));
-        const float s1 = fmaxf(0.f, 1.f - fabsf(r1 - (float)m));
-        S0[m] = s0;
+        const float s0 = clamp01(1.f - fabsf(r0 - (float)m));
+        const float s1 = clamp01(1.f - fabsf(r1 - (float)m));
         dS[m] = s1 - s0;
+        f.A[m] = 0.5f * (s0 + s1);
+        f.D[m] = RSQRT12 * dS[m];
     }
+    f.P[0] = dS[0];
+    f.P[1] = dS[0] + dS[1];
+    return f;
 }
 
 // Slot s (0..53) of the deposit window: component and offsets from the base node.
@@ -185,48 +204,14 @@ __device__ __forceinline__ void slot_geom(int s, int &comp, int &oi, int &oj, in
     }
 }
 
-// Esirkepov factors of one move: the running sum of dS along each current's
-// own axis (pre[axis][edge]) and the transverse weight
-//   T = S0 S0' + (dS S0' + S0 dS')/2 + dS dS'/3 = A A' + dS dS'/12,  A = S0 + dS/2,
-// of the other two axes.  Slot s has current pre * T.  Every index used
-// below is a compile-time constant after unrolling, so nothing leaves
-// registers.
-struct Dep {
-    float pre[3][2];
-    float Tyz[3][3], Txz[3][3], Txy[3][3];
-};
-
-__device__ __forceinline__ void make_dep(const float S0[3][3], const float dS[3][3], Dep &d)
-{
-    float A[3][3], D[3][3];
-#pragma unroll
-    for (int ax = 0; ax < 3; ++ax) {
-        d.pre[ax][0] = dS[ax][0];
-        d.pre[ax][1] = dS[ax][0] + dS[ax][1];
-#pragma unroll
-        for (int m = 0; m < 3; ++m) {
-            A[ax][m] = S0[ax][m] + 0.5f * dS[ax][m];
-            D[ax][m] = (1.f / 12.f) * dS[ax][m];
-        }
-    }
-#pragma unroll
-    for (int p = 0; p < 3; ++p)
-#pragma unroll
-        for (int q = 0; q < 3; ++q) {
-            d.Tyz[p][q] = A[1][p] * A[2][q] + D[1][p] * dS[2][q];
-            d.Txz[p][q] = A[0][p] * A[2][q] + D[0][p] * dS[2][q];
-            d.Txy[p][q] = A[0][p] * A[1][q] + D[0][p] * dS[1][q];
-        }
-}
-
-// Current of slot s, scaled by f.
-__device__ __forceinline__ float slot_value(const Dep &d, int s, float f)
+// Current of slot s of a move with factors fx, fy, fz, per unit charge factor.
+__device__ __forceinline__ float slot_value(const AxisF &fx, const AxisF &fy, const AxisF &fz, int s)
 {
     int comp, oi, oj, ok;
     slot_geom(s, comp, oi, oj, ok);
-    if (comp == 0) return f * d.pre[0][oi] * d.Tyz[oj][ok];
-    if (comp == 1) return f * d.pre[1][oj] * d.Txz[oi][ok];
-    return f * d.pre[2][ok] * d.Txy[oi][oj];
+    if (comp == 0) return fx.P[oi] * (fy.A[oj] * fz.A[ok] + fy.D[oj] * fz.D[ok]);
+    if (comp == 1) return fy.P[oj] * (fx.A[oi] * fz.A[ok] + fx.D[oi] * fz.D[ok]);
+    return fz.P[ok] * (fx.A[oi] * fy.A[oj] + fx.D[oi] * fy.D[oj]);
 }
 
 // Cell index of slot s of the window at (bx, by, bz) after wrapping, or -1
@@ -245,16 +230,6 @@ __device__ __forceinline__ int slot_index(const PartArgs &a, int s, int bx, int 
     return i + a.nx * (j + a.ny * k);
 }
 
-__device__ __forceinline__ float *slot_addr(const PartArgs &a, int s, int bx, int by, int bz)
-{
-    int comp;
-    const int q = slot_index(a, s, bx, by, bz, comp);
-    if (q < 0) return nullptr;
-    // select, not a[comp]: a runtime index into the argument block would put it in scratch
-    float *J = comp == 0 ? a.Jb[0] : (comp == 1 ? a.Jb[1] : a.Jb[2]);
-    return J + q;
-}
-
 // Fixed-point deposit: each particle's slot currents are rounded to integer
 // units (qscale per V/m, at most 2^24 per slot) before anything is summed, so
 // the wavefront sums (at most 2^30) and the 64-bit atomics are exact and the
@@ -265,259 +240,234 @@ __device__ __forceinline__ void add_fixed(const PartArgs &a, int comp, int q, in
     gatomic_add(G(J) + q, (unsigned long long)(long long)units);
 }
 
-// Sum of two slot values: FP32, or the int32 fixed-point units held in the
-// same registers.
-template <int INT>
-__device__ __forceinline__ float add2(float x, float y)
-{
-    return INT ? __int_as_float(__float_as_int(x) + __float_as_int(y)) : x + y;
-}
-
 // Lane l receives x from lane l ^ OFF (OFF = 8, 4, 2, 1), by DPP row moves.
 template <int OFF>
-__device__ __forceinline__ float xor_lane(float x)
+__device__ __forceinline__ int xor_lane(int v)
 {
-    const int v = __float_as_int(x);
-    int r;
-    if (OFF == 8) {
-        r = __builtin_amdgcn_update_dpp(0, v, 0x128, 0xf, 0xf, false);  // row_ror:8
-    } else if (OFF == 4) {
+    if (OFF == 8) return __builtin_amdgcn_update_dpp(0, v, 0x128, 0xf, 0xf, false);  // row_ror:8
+    if (OFF == 4) {
         // lanes with bit 2 clear (banks 0, 2) read l + 4, the others l - 4
         const int t = __builtin_amdgcn_update_dpp(0, v, 0x104, 0xf, 0x5, false);  // row_shl:4
-        r = __builtin_amdgcn_update_dpp(t, v, 0x114, 0xf, 0xa, false);            // row_shr:4
-    } else if (OFF == 2) {
-        r = __builtin_amdgcn_update_dpp(0, v, 0x4e, 0xf, 0xf, false);  // quad_perm [2,3,0,1]
-    } else {
-        r = __builtin_amdgcn_update_dpp(0, v, 0xb1, 0xf, 0xf, false);  // quad_perm [1,0,3,2]
+        return __builtin_amdgcn_update_dpp(t, v, 0x114, 0xf, 0xa, false);         // row_shr:4
     }
-    return __int_as_float(r);
+    if (OFF == 2) return __builtin_amdgcn_update_dpp(0, v, 0x4e, 0xf, 0xf, false);  // quad_perm [2,3,0,1]
+    return __builtin_amdgcn_update_dpp(0, v, 0xb1, 0xf, 0xf, false);                // quad_perm [1,0,3,2]
 }
 
-template <int OFF, int INT>
-__device__ __forceinline__ void halve_dpp(float *v, int lane)
+template <int OFF>
+__device__ __forceinline__ void halve_dpp(int *v, int lane)
 {
     const bool up = (lane & OFF) != 0;
 #pragma unroll
     for (int e = 0; e < OFF; ++e) {
-        const float send = up ? v[e] : v[e + OFF];
-        const float keep = up ? v[e + OFF] : v[e];
-        v[e] = add2<INT>(keep, xor_lane<OFF>(send));
+        const int send = up ? v[e] : v[e + OFF];
+        const int keep = up ? v[e + OFF] : v[e];
+        v[e] = keep + xor_lane<OFF>(send);
     }
 }
 
-// Rounds of width 32 and 16: the lower half-wave keeps slot e, the upper
-// keeps slot e + OFF; a half-wave swap of the two registers puts each half's
-// partner values next to its own, and the sum finishes the round.  The first
-// round reads the 54 slot currents of a lane, or zeros for a lane outside
-// the round's window.
-template <int INT>
-__device__ __forceinline__ void halve32(const float *val, bool mine, float *v)
+// Sum of the lanes' 54 fixed-point slot currents over the lanes with `mine`
+// set: lane l ends with slot l.  Rounds of width 32 and 16: the lower half-wave
+// keeps slot e, the upper keeps slot e + OFF; a half-wave swap of the two
+// registers puts each half's partner values next to its own, and the sum
+// finishes the round.  The first round reads zeros for a lane outside.
+__device__ __forceinline__ int wave_reduce64(const int *val, bool mine, int lane)
 {
+    int v[32];
 #pragma unroll
     for (int e = 0; e < 32; ++e) {
-        const float lo = mine ? val[e] : 0.f;
-        const float hi = (e + 32 < 54 && mine) ? val[e + 32 < 54 ? e + 32 : 0] : 0.f;
-        const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(lo), __float_as_uint(hi), false, false);
-        v[e] = add2<INT>(__uint_as_float(r[0]), __uint_as_float(r[1]));
+        const int lo = mine ? val[e] : 0;
+        const int hi = (e + 32 < 54 && mine) ? val[e + 32 < 54 ? e + 32 : 0] : 0;
+        const auto r = __builtin_amdgcn_permlane32_swap((unsigned)lo, (unsigned)hi, false, false);
+        v[e] = (int)(r[0] + r[1]);
     }
-}
-
-template <int INT>
-__device__ __forceinline__ void halve16(float *v)
-{
 #pragma unroll
     for (int e = 0; e < 16; ++e) {
-        const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v[e]), __float_as_uint(v[e + 16]),
-                                                        false, false);
-        v[e] = add2<INT>(__uint_as_float(r[0]), __uint_as_float(r[1]));
+        const auto r = __builtin_amdgcn_permlane16_swap((unsigned)v[e], (unsigned)v[e + 16], false, false);
+        v[e] = (int)(r[0] + r[1]);
     }
-}
-
-// After the six rounds lane l holds the sum of slot l over the lanes with
-// `mine` set.
-template <int INT>
-__device__ __forceinline__ float wave_reduce64(const float *val, bool mine, int lane)
-{
-    float v[32];
-    halve32<INT>(val, mine, v);
-    halve16<INT>(v);
-    halve_dpp<8, INT>(v, lane);
-    halve_dpp<4, INT>(v, lane);
-    halve_dpp<2, INT>(v, lane);
-    halve_dpp<1, INT>(v, lane);
+    halve_dpp<8>(v, lane);
+    halve_dpp<4>(v, lane);
+    halve_dpp<2>(v, lane);
+    halve_dpp<1>(v, lane);
     return v[0];
 }
 
-// A window shared by at least ROUND_LANES lanes is summed by a wavefront
-// round (about 220 VALU instructions, then one atomic per slot); the lanes of
-// smaller windows add their slots with per-lane atomics, all such lanes of the
-// wavefront together (54 atomic instructions however many lanes).
-constexpr int ROUND_LANES = 3;
+// Where the three nodes of a window along one axis are stored: linear offsets,
+// and whether the node is inside the grid (after wrapping).
+struct AxisO {
+    int o[3];
+    bool ok[3];
+};
 
-// ---- row-union deposit ----
-// A wavefront whose windows share their y and z base and differ only in x
-// (consecutive sorted particles in one grid row, the usual case away from the
-// bunch core) spans a union of windows along x.  Inclusive prefix sums of the
-// 54 slot currents are taken over the wavefront's lanes (six DPP adds per
-// slot), so a run of lanes with the same window sums to P(its last lane) -
-// P(the last lane of the run before it).  When every window has one run (the
-// lanes are sorted), the last lane of each run stores its P as the block of
-// its window in tile `plus` and as the block of the next run's window in tile
-// `minus`: plain LDS stores of whole blocks, no LDS atomics (which issue
-// slowly even when their addresses differ).  Each entry of the union then
-// sums, over the up to three windows covering it, plus - minus of the slot it
-// is in those windows, and goes to J_b in a few coalesced atomic
-// instructions, however many windows the wavefront has.  Lanes that do not
-// deposit carry zeros and a key of -1: their runs store nothing in `plus` and
-// pass the running sum on to `minus`.
-constexpr int UNION_KEYS = 14;           // window bases a union may span
-constexpr int UNION_XW = UNION_KEYS + 2;  // x nodes of the widest union
-// floats per window: 54 slots, 16-byte aligned, and an odd number of 16-byte
-// groups so the readback's lanes (one window apart) fall in different banks
-constexpr int UNION_BLOCK = 60;
-// two zero blocks on each side: the readback's window index t - a runs over
-// -2 .. UNION_XW - 1 without a test
-constexpr int UNION_PAD = 2;
-constexpr int UNION_TILE = (UNION_KEYS + 2 * UNION_PAD) * UNION_BLOCK;
-
-// Reductions over the wavefront in the usual GFX9 pattern: prefix within
-// 16-lane rows, then the row broadcasts; the result is valid at lane 63.
-__device__ __forceinline__ int wave_min_dpp(int v)
+__device__ __forceinline__ AxisO axis_offsets(int base, int n, int per, int stride)
 {
-    v = min(v, __builtin_amdgcn_update_dpp(INT_MAX, v, 0x111, 0xf, 0xf, false));  // row_shr:1
-    v = min(v, __builtin_amdgcn_update_dpp(INT_MAX, v, 0x112, 0xf, 0xf, false));  // row_shr:2
-    v = min(v, __builtin_amdgcn_update_dpp(INT_MAX, v, 0x114, 0xf, 0xf, false));  // row_shr:4
-    v = min(v, __builtin_amdgcn_update_dpp(INT_MAX, v, 0x118, 0xf, 0xf, false));  // row_shr:8
-    v = min(v, __builtin_amdgcn_update_dpp(INT_MAX, v, 0x142, 0xa, 0xf, false));  // row_bcast:15
-    v = min(v, __builtin_amdgcn_update_dpp(INT_MAX, v, 0x143, 0xc, 0xf, false));  // row_bcast:31
-    return __builtin_amdgcn_readlane(v, 63);
-}
-
-__device__ __forceinline__ unsigned wave_or_dpp(unsigned v)
-{
-    v |= __builtin_amdgcn_update_dpp(0u, v, 0x111, 0xf, 0xf, false);
-    v |= __builtin_amdgcn_update_dpp(0u, v, 0x112, 0xf, 0xf, false);
-    v |= __builtin_amdgcn_update_dpp(0u, v, 0x114, 0xf, 0xf, false);
-    v |= __builtin_amdgcn_update_dpp(0u, v, 0x118, 0xf, 0xf, false);
-    v |= __builtin_amdgcn_update_dpp(0u, v, 0x142, 0xa, 0xf, false);
-    v |= __builtin_amdgcn_update_dpp(0u, v, 0x143, 0xc, 0xf, false);
-    return __builtin_amdgcn_readlane(v, 63);
-}
-
-// Inclusive prefix sum over the wavefront's lanes: prefix sums within the
-// 16-lane rows (DPP row shifts, each fused into its add), then the row
-// totals carried across rows.  The two cross-row steps add lane 15 of rows 0
-// and 2 to rows 1 and 3, then lane 31 to rows 2 and 3; each is one DPP add
-// that leaves the other rows untouched, written out because the compiler
-// splits a row-masked DPP add into three instructions.  A DPP read of a VGPR
-// that a VALU instruction has just written needs two wait states: the s_nops.
-__device__ __forceinline__ float wave_prefix(float v)
-{
-#define PIC_PREFIX_STEP(ctrl)                                                                                 \
-    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), ctrl, 0xf, 0xf, true))
-    PIC_PREFIX_STEP(0x111);  // row_shr:1
-    PIC_PREFIX_STEP(0x112);  // row_shr:2
-    PIC_PREFIX_STEP(0x114);  // row_shr:4
-    PIC_PREFIX_STEP(0x118);  // row_shr:8
-#undef PIC_PREFIX_STEP
-    asm("s_nop 1\n\t"
-        "v_add_f32_dpp %0, %0, %0 row_bcast:15 row_mask:0xa bank_mask:0xf\n\t"
-        "s_nop 1\n\t"
-        "v_add_f32_dpp %0, %0, %0 row_bcast:31 row_mask:0xc bank_mask:0xf"
-        : "+v"(v));
-    return v;
-}
-
-// Store the 54 values as the block of window k (relative to the union's
-// first base) of a tile.
-__device__ __forceinline__ void union_store(float *tile, int k, const float *val)
-{
-    float4 *d = reinterpret_cast<float4 *>(tile + (k + UNION_PAD) * UNION_BLOCK);
+    AxisO r;
 #pragma unroll
-    for (int q = 0; q < 13; ++q) d[q] = make_float4(val[4 * q], val[4 * q + 1], val[4 * q + 2], val[4 * q + 3]);
-    reinterpret_cast<float2 *>(tile + (k + UNION_PAD) * UNION_BLOCK)[26] = make_float2(val[52], val[53]);
-}
-
-// Union entries of one current component: x position t (0 .. UNION_XW - 1
-// from the first base) and R transverse offsets (r = 0 .. R-1, y-major with NZ
-// z offsets per y offset); the window at base t - a holds the entry as slot
-// S0 + a * SA + r.  All LDS reads are issued first (windows outside the union
-// read the zero padding), then the sums, then one atomic add per nonzero sum;
-// the component is a template argument so that J stays a plain pointer.
-template <int S0, int SA, int NA, int R, int NZ>
-__device__ __forceinline__ void union_flush(float *J, const float *plus, const float *minus, int lane, int base,
-                                            int sy, int sz)
-{
-    constexpr int N = R * UNION_XW;
-    constexpr int IT = (N + 63) / 64;
-    float pv[IT][NA], mv[IT][NA];
-#pragma unroll
-    for (int it = 0; it < IT; ++it) {
-        const int e = min(it * 64 + lane, N - 1);
-        const int t = e % UNION_XW, r = e / UNION_XW;
-#pragma unroll
-        for (int a = 0; a < NA; ++a) {
-            const int q = (t - a + UNION_PAD) * UNION_BLOCK + S0 + a * SA + r;
-            pv[it][a] = plus[q];
-            mv[it][a] = minus[q];
-        }
+    for (int m = 0; m < 3; ++m) {
+        const int i = per ? wrapn(base + m, n) : base + m;
+        r.ok[m] = i >= 0 && i < n;
+        r.o[m] = r.ok[m] ? i * stride : 0;
     }
-#pragma unroll
-    for (int it = 0; it < IT; ++it) {
-        const int e = it * 64 + lane;
-        const int t = e % UNION_XW, r = e / UNION_XW;
-        float v = 0.f;
-#pragma unroll
-        for (int a = 0; a < NA; ++a) v += pv[it][a] - mv[it][a];
-        if (e < N && v != 0.f) gatomic_add(G(J) + base + t + sy * (r / NZ) + sz * (r % NZ), v);
-    }
+    return r;
 }
 
-// Deposit of a wavefront whose depositing lanes all have window base
-// (bx, by, bz) with the same by, bz, bxmin <= bx < bxmin + UNION_KEYS, the
-// union inside the grid, and one run of lanes per window.  val: the lane's 54
-// slot currents (0 where it does not deposit); key: bx - bxmin, or -1 for a
-// lane that does not deposit; knext: the key of lane + 1 (-1 past lane 63);
-// last: the lane ends its run.
-__device__ __forceinline__ void deposit_union(const PartArgs &a, float *val, int lane, int key, int knext,
-                                              bool last, int bxmin, int by, int bz, float *plus, float *minus,
-                                              bool ycross, bool zcross)
+// Window slots of one lane added with per-lane atomics: v(s) is the lane's
+// current of slot s, add(comp, cell, v) the atomic.
+template <class V, class Add>
+__device__ __forceinline__ void lane_deposit(const PartArgs &a, const int base[3], V v, Add add)
 {
-    // one wavefront per workgroup: its LDS operations execute in program
-    // order, and the wave barriers keep the compiler from moving the tiles'
-    // accesses of one phase into another
-    constexpr int N4 = UNION_TILE / 4;
-    for (int e = lane; e < N4; e += 64) {
-        reinterpret_cast<float4 *>(plus)[e] = make_float4(0.f, 0.f, 0.f, 0.f);
-        reinterpret_cast<float4 *>(minus)[e] = make_float4(0.f, 0.f, 0.f, 0.f);
-    }
-    // a slot at node offset 2 along y (z) is exactly 0 for a move that stays
-    // in one y (z) cell: when no lane crosses, its prefix sums are 0 as well
+    const AxisO ox = axis_offsets(base[0], a.nx, a.per[0], 1);
+    const AxisO oy = axis_offsets(base[1], a.ny, a.per[1], a.nx);
+    const AxisO oz = axis_offsets(base[2], a.nz, a.per[2], a.nx * a.ny);
 #pragma unroll
     for (int s = 0; s < 54; ++s) {
         int comp, oi, oj, ok;
         slot_geom(s, comp, oi, oj, ok);
-        const bool y2 = comp != 1 && oj == 2, z2 = comp != 2 && ok == 2;
-        if ((y2 && !ycross) || (z2 && !zcross)) continue;
-        val[s] = wave_prefix(val[s]);
+        const auto c = v(s);
+        if (c != 0 && ox.ok[oi] && oy.ok[oj] && oz.ok[ok]) add(comp, ox.o[oi] + oy.o[oj] + oz.o[ok], c);
     }
-    __builtin_amdgcn_wave_barrier();
-    if (last && key >= 0) union_store(plus, key, val);
-    if (last && knext >= 0) union_store(minus, knext, val);
-    __builtin_amdgcn_wave_barrier();
-    const int base = bxmin + a.nx * (by + a.ny * bz);
-    const int sy = a.nx, sz = a.nx * a.ny;
-    // the current arrays' addresses held in scalar registers through the
-    // flush (otherwise each conditional atomic reloads its pointer from the
-    // argument block and waits for it)
-    float *J0 = a.Jb[0], *J1 = a.Jb[1], *J2 = a.Jb[2];
-    asm volatile("" : "+s"(J0), "+s"(J1), "+s"(J2));
-    // slots: Jx a*9 + b*3 + c (a edge, b, c nodes); Jy 18 + a*6 + m*3 + c;
-    // Jz 36 + a*6 + b*2 + m (a x node, m edge)
-    union_flush<0, 9, 2, 9, 3>(J0, plus, minus, lane, base, sy, sz);
-    union_flush<18, 6, 3, 6, 3>(J1, plus, minus, lane, base, sy, sz);
-    union_flush<36, 6, 3, 6, 2>(J2, plus, minus, lane, base, sy, sz);
 }
+
+// ---- deposit of the lanes of one grid row (matrix cores) ----
+// The lanes of a pass share their windows' y and z base (by, bz) and have x
+// bases in [X0, X0 + 13], so their windows lie on 16 x nodes X0 + t.  Every
+// edge current is a sum over the particles p of (x factor at t) times
+// (transverse factor of the slot):
+//   Jx[b, c](t) = sum_p Px[p](t) (Ay[p,b] Az[p,c] + Dy[p,b] Dz[p,c])
+//   Jy[m, c](t) = sum_p Ax[p](t) Py[p,m] Az[p,c] + Dx[p](t) Py[p,m] Dz[p,c]
+//   Jz[m, b](t) = sum_p Ax[p](t) Pz[p,m] Ay[p,b] + Dx[p](t) Pz[p,m] Dy[p,b]
+// v_mfma_f32_16x16x4_f32 takes 4 particles at a time: rows are slots (the 9 of
+// Jx; the 6 + 6 of Jy and Jz), columns the 16 x nodes.  Lane l holds row or
+// column l % 16 of particle l / 16, so the particles' factors pass from their
+// own lanes through LDS, and the x factors are evaluated at node t from x0, x1
+// (a particle outside the pass is put far away, where they are 0).  Products
+// and sums are FP32, each sum of at most 64 terms.
+//
+// The push issues VALU at most of its peak, so what counts is instructions: a
+// pass takes about 220 VALU and 48 MFMA (1536 matrix-core cycles, beside other
+// wavefronts' VALU) whatever the number and order of the windows, where summing
+// every slot over the lanes takes 324 for one ordered row and 220 per window
+// otherwise.  512x256x256 cells, 1e7 particles: 351 -> 276 us per launch; 1e6
+// particles in a 64x128x128 box periodic along x: 94 -> 63 us; 4000 particles
+// (63 wavefronts, one cell across y): 22.5 -> 14.8 us.
+constexpr int ROW_NODES = 16;
+constexpr int ROW_BASES = ROW_NODES - 2;
+// Rows with fewer lanes go to the per-lane atomics.
+constexpr int ROW_LANES = 3;
+
+typedef float fvec4 __attribute__((ext_vector_type(4)));
+
+struct RowLds {
+    float4 pair[64][3];  // per particle (A, D) at y nodes 0..2, then z nodes 0..2
+    float4 pre[64];      // Py[0], Py[1], Pz[0], Pz[1]
+    float2 x[64];        // x0, x1
+};
+
+__device__ __forceinline__ void row_factors(RowLds &L, int lane, const AxisF &fy, const AxisF &fz)
+{
+    L.pair[lane][0] = make_float4(fy.A[0], fy.D[0], fy.A[1], fy.D[1]);
+    L.pair[lane][1] = make_float4(fy.A[2], fy.D[2], fz.A[0], fz.D[0]);
+    L.pair[lane][2] = make_float4(fz.A[1], fz.D[1], fz.A[2], fz.D[2]);
+    L.pre[lane] = make_float4(fy.P[0], fy.P[1], fz.P[0], fz.P[1]);
+}
+
+// m: the pass's lanes; yz: some lane of the wavefront moves along y or z.
+__device__ __forceinline__ void deposit_rows(const PartArgs &a, RowLds &L, unsigned long long m, bool mine, int lane,
+                                             float x0, float x1, int X0, int by, int bz, bool yz)
+{
+    const float far = 1e9f;
+    // one wavefront per workgroup: its LDS operations execute in program
+    // order, the wave barriers keep the compiler from moving them
+    __builtin_amdgcn_wave_barrier();
+    L.x[lane] = mine ? make_float2(x0, x1) : make_float2(far, far);
+    __builtin_amdgcn_wave_barrier();
+    const int t = lane & 15, q = lane >> 4;
+    // Row t of Jx is (b, c) = (t/2, t%3) for t < 6 and (t - 6, 8 - t) for t =
+    // 6..8; row t of Jy, Jz is edge m = t/3, z node c = t%3 of Jy for t < 6,
+    // edge (t-6)/3, y node (t-6)%3 of Jz for t = 6..11.  So both use the pair n1
+    // (the Jy / Jz row's node), Jx with the other axis's pair n2.
+    const int n1 = t < 6 ? 3 + t % 3 : (t < 12 ? (t - 6) % 3 : 0);
+    const int n2 = t < 6 ? t >> 1 : (t < 9 ? 11 - t : 0);
+    const int np = min(t / 3, 3);
+    const float2 *pairs = reinterpret_cast<const float2 *>(L.pair) + q * 6;
+    const float *pres = reinterpret_cast<const float *>(L.pre) + q * 4 + np;
+    const float ct = (float)(X0 + t);
+    fvec4 jx = {0.f, 0.f, 0.f, 0.f}, jyz = {0.f, 0.f, 0.f, 0.f};
+    for (int d = 0; d < 4; ++d) {
+        if (!((m >> (16 * d)) & 0xffffull)) continue;
+        float2 v1[4], v2[4], xx[4];
+        float pr[4];
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            const int p = 16 * d + 4 * g;
+            v1[g] = pairs[p * 6 + n1];
+            v2[g] = pairs[p * 6 + n2];
+            xx[g] = L.x[p + q];
+            pr[g] = pres[p * 4];
+        }
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            const float e0 = xx[g].x - ct, e1 = xx[g].y - ct;
+            // running sums of the shapes up to node t, after less before
+            const float px = clamp01(1.f - e1) - clamp01(1.f - e0);
+            const float T = v1[g].x * v2[g].x + v1[g].y * v2[g].y;
+            jx = __builtin_amdgcn_mfma_f32_16x16x4f32(T, px, jx, 0, 0, 0);
+            if (yz) {
+                const float s0 = clamp01(1.f - fabsf(e0)), s1 = clamp01(1.f - fabsf(e1));
+                // 2 A and 2 D along x: the factor 1/2 is applied to the sums
+                jyz = __builtin_amdgcn_mfma_f32_16x16x4f32(pr[g] * v1[g].x, s0 + s1, jyz, 0, 0, 0);
+                jyz = __builtin_amdgcn_mfma_f32_16x16x4f32(pr[g] * v1[g].y, (2.f * RSQRT12) * (s1 - s0), jyz, 0, 0, 0);
+            }
+        }
+    }
+    // lane l holds column t of rows 4 q + j, j = 0..3: the rows' transverse
+    // offsets (oj | ok << 2) packed four to a word, by q
+    const int wx = q == 0 ? 0x1940 : (q == 1 ? 0x58a6 : 0x0002);
+    const int wyz = q == 0 ? 0x1840 : (q == 1 ? 0x1095 : 0x6542);
+    const int nxr = q < 2 ? 4 : (q == 2 ? 1 : 0), nyzr = q < 3 ? 4 : 0;
+    const int sy = a.nx, sz = a.nx * a.ny;
+    const bool inside = X0 >= 0 && X0 + ROW_NODES <= a.nx && by >= 0 && by + 2 < a.ny && bz >= 0 && bz + 2 < a.nz;
+    const float qd = a.qd;
+    if (inside) {
+        const int cell = X0 + a.nx * (by + a.ny * bz) + t;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int o = cell + sy * ((wx >> (4 * j)) & 3) + sz * ((wx >> (4 * j + 2)) & 3);
+            if (j < nxr && jx[j] != 0.f) gatomic_add(G(a.Jb[0]) + o, qd * jx[j]);
+        }
+        if (yz) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int o = cell + sy * ((wyz >> (4 * j)) & 3) + sz * ((wyz >> (4 * j + 2)) & 3);
+                float *J = 4 * q + j < 6 ? a.Jb[1] : a.Jb[2];
+                if (j < nyzr && jyz[j] != 0.f) gatomic_add(G(J) + o, (0.5f * qd) * jyz[j]);
+            }
+        }
+    } else {
+        const int i = a.per[0] ? wrapn(X0 + t, a.nx) : X0 + t;
+        const bool okx = i >= 0 && i < a.nx;
+        const AxisO oy = axis_offsets(by, a.ny, a.per[1], sy), oz = axis_offsets(bz, a.nz, a.per[2], sz);
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const int w = ((j < 4 ? wx : wyz) >> (4 * (j & 3))) & 15;
+            const int oj = w & 3, ok = w >> 2;
+            const int o = i + (oj == 0 ? oy.o[0] : (oj == 1 ? oy.o[1] : oy.o[2])) +
+                          (ok == 0 ? oz.o[0] : (ok == 1 ? oz.o[1] : oz.o[2]));
+            const bool in = okx && (oj == 0 ? oy.ok[0] : (oj == 1 ? oy.ok[1] : oy.ok[2])) &&
+                            (ok == 0 ? oz.ok[0] : (ok == 1 ? oz.ok[1] : oz.ok[2]));
+            const float v = j < 4 ? jx[j & 3] : jyz[j & 3];
+            float *J = j < 4 ? a.Jb[0] : (4 * q + (j & 3) < 6 ? a.Jb[1] : a.Jb[2]);
+            if (in && (j & 3) < (j < 4 ? nxr : nyzr) && v != 0.f) gatomic_add(G(J) + o, (j < 4 ? qd : 0.5f * qd) * v);
+        }
+    }
+}
+
+// Fixed-point deposit: a window shared by at least ROUND_LANES lanes is summed
+// by a wavefront round (about 220 VALU instructions, then one atomic per slot);
+// the lanes of smaller windows add their slots with per-lane atomics, all such
+// lanes of the wavefront together (54 atomic instructions however many lanes).
+constexpr int ROUND_LANES = 3;
 
 template <int MODE, int PX, int FIX>
 __device__ __forceinline__ void push_body(const PartArgs &a, int blk)
@@ -534,11 +484,8 @@ __device__ __forceinline__ void push_body(const PartArgs &a, int blk)
     const gp<float> __restrict__ UY = G(st->P[4]);
     const gp<float> __restrict__ UZ = G(st->P[5]);
     bool dep = false;
-    // zeroed: a lane that does not deposit is silenced by a factor 0 in the
-    // wavefront sum, and 0 x (uninitialised register) could be NaN
-    Dep d = {};
     int base[3] = {0, 0, 0};
-    bool ycross = false, zcross = false;  // the move leaves its y (z) cell
+    float x0 = 0.f, y0 = 0.f, z0 = 0.f, x1 = 0.f, y1 = 0.f, z1 = 0.f;  // the move, x1 before folding
     if (p < a.n) {
         // The gather and Boris run for every lane, with no branch on liveness
         // before them, so that all six particle loads go out together (a
@@ -594,49 +541,33 @@ __device__ __forceinline__ void push_body(const PartArgs &a, int blk)
         }
         if (live) {
             const float g = rsqrtf(1.f + u0 * u0 + u1 * u1 + u2 * u2);
-            float x1 = x + a.S * u0 * g, y1 = y + a.S * u1 * g, z1 = z + a.S * u2 * g;
+            const float nx1 = x + a.S * u0 * g, ny1 = y + a.S * u1 * g, nz1 = z + a.S * u2 * g;
             // leaving through a wall, or a non-finite move, deactivates the particle
-            const bool out = !(isfinite(x1) && isfinite(y1) && isfinite(z1)) ||
-                             (!a.per[0] && !(x1 >= 0.f && x1 < (float)a.nx)) ||
-                             (!a.per[1] && !(y1 >= 0.f && y1 < (float)a.ny)) ||
-                             (!a.per[2] && !(z1 >= 0.f && z1 < (float)a.nz));
+            const bool out = !(isfinite(nx1) && isfinite(ny1) && isfinite(nz1)) ||
+                             (!a.per[0] && !(nx1 >= 0.f && nx1 < (float)a.nx)) ||
+                             (!a.per[1] && !(ny1 >= 0.f && ny1 < (float)a.ny)) ||
+                             (!a.per[2] && !(nz1 >= 0.f && nz1 < (float)a.nz));
             __builtin_nontemporal_store(u0, UX + p);
             __builtin_nontemporal_store(u1, UY + p);
             __builtin_nontemporal_store(u2, UZ + p);
             if (out) {
                 __builtin_nontemporal_store(-1.f, X + p);  // left the box: deactivated, last move not deposited
             } else {
-                // written out per axis: constant indices keep S0/dS in registers
-                float S0[3][3], dS[3][3];
-                base[0] = min((int)floorf(x), (int)floorf(x1));
-                base[1] = min((int)floorf(y), (int)floorf(y1));
-                base[2] = min((int)floorf(z), (int)floorf(z1));
-                ycross = (int)floorf(y) != (int)floorf(y1);
-                zcross = (int)floorf(z) != (int)floorf(z1);
-                shapes(x, x1, base[0], S0[0], dS[0]);
-                shapes(y, y1, base[1], S0[1], dS[1]);
-                shapes(z, z1, base[2], S0[2], dS[2]);
-                make_dep(S0, dS, d);
+                x0 = x;
+                y0 = y;
+                z0 = z;
+                x1 = nx1;
+                y1 = ny1;
+                z1 = nz1;
+                base[0] = min((int)floorf(x0), (int)floorf(x1));
+                base[1] = min((int)floorf(y0), (int)floorf(y1));
+                base[2] = min((int)floorf(z0), (int)floorf(z1));
                 dep = true;
-                if (a.per[0]) x1 = fold(x1, a.nx);
-                if (a.per[1]) y1 = fold(y1, a.ny);
-                if (a.per[2]) z1 = fold(z1, a.nz);
-                __builtin_nontemporal_store(x1, X + p);
-                __builtin_nontemporal_store(y1, Y + p);
-                __builtin_nontemporal_store(z1, Z + p);
+                __builtin_nontemporal_store(a.per[0] ? fold(x1, a.nx) : x1, X + p);
+                __builtin_nontemporal_store(a.per[1] ? fold(y1, a.ny) : y1, Y + p);
+                __builtin_nontemporal_store(a.per[2] ? fold(z1, a.nz) : z1, Z + p);
             }
         }
-    }
-    // the 54 slot currents of this particle's move (0 for a lane that does not deposit)
-    const float qd = a.qd;
-    float val[54];
-#pragma unroll
-    for (int s = 0; s < 54; ++s) val[s] = slot_value(d, s, qd);
-    if (FIX) {
-        // integer units per slot, kept in the same registers
-        const float qs = a.qscale;
-#pragma unroll
-        for (int s = 0; s < 54; ++s) val[s] = __int_as_float(__float2int_rn(val[s] * qs));
     }
     const unsigned long long live = __ballot(dep);
     // per-wavefront push counter (one slot per wavefront of the launch)
@@ -644,39 +575,21 @@ __device__ __forceinline__ void push_body(const PartArgs &a, int blk)
     // counter's old value as a load-add-store would)
     if (lane == 0 && live) gatomic_add(G(a.pushes) + (p >> 6), (unsigned long long)__popcll(live));
     unsigned long long rem = live;
-    if (MODE == 0 && !FIX && live) {
-        // one grid row of windows spanning at least two x bases: the row-union tiles
-        __shared__ float4 tplus4[UNION_TILE / 4], tminus4[UNION_TILE / 4];
-        const int leader = __ffsll((long long)live) - 1;
-        const int by0 = __builtin_amdgcn_readlane(base[1], leader);
-        const int bz0 = __builtin_amdgcn_readlane(base[2], leader);
-        if (__ballot(dep && (base[1] != by0 || base[2] != bz0)) == 0ull) {
-            const int bxmin = wave_min_dpp(dep ? base[0] : INT_MAX);
-            const int bxmax = -wave_min_dpp(dep ? -base[0] : INT_MAX);
-            const bool inside = bxmin >= 0 && bxmax + 2 < a.nx && by0 >= 0 && by0 + 2 < a.ny && bz0 >= 0 &&
-                                bz0 + 2 < a.nz;
-            if (inside && bxmax > bxmin && bxmax - bxmin < UNION_KEYS) {
-                const int key = dep ? base[0] - bxmin : -1;
-                const int knext = __builtin_amdgcn_update_dpp(-1, key, 0x130, 0xf, 0xf, false);  // wave_shl:1
-                const bool last = lane == 63 || knext != key;
-                // one run per window: as many runs as windows
-                const unsigned keys = wave_or_dpp(last && key >= 0 ? 1u << key : 0u);
-                if (__popc(keys) == __popcll(__ballot(last && key >= 0))) {
-                    deposit_union(a, val, lane, key, knext, last, bxmin, by0, bz0, (float *)tplus4,
-                                  (float *)tminus4, __ballot(dep && ycross) != 0ull,
-                                  __ballot(dep && zcross) != 0ull);
-                    rem = 0;
-                }
-            }
-        }
-    }
-    if (MODE != 1 && rem) {
+    if (!live) return;
+    if (FIX) {
+        // integer units per slot (0 for a lane that does not deposit), each
+        // computed once whichever way it is added: the sums do not depend on
+        // which lanes share a round
+        const AxisF fx = axis_factors(x0, x1, base[0]), fy = axis_factors(y0, y1, base[1]),
+                    fz = axis_factors(z0, z1, base[2]);
+        int val[54];
+#pragma unroll
+        for (int s = 0; s < 54; ++s) val[s] = __float2int_rn(a.qd * slot_value(fx, fy, fz, s) * a.qscale);
         // lane l < 54 owns slot l of every round's window: its component and
         // offset from the window's base node, computed once
         int lc, li, lj, lk;
         slot_geom(lane < 54 ? lane : 0, lc, li, lj, lk);
         const int lrel = li + a.nx * (lj + a.ny * lk);
-        float *Jl = lc == 0 ? a.Jb[0] : (lc == 1 ? a.Jb[1] : a.Jb[2]);
         const int key = (base[0] + 1) + (a.nx + 2) * ((base[1] + 1) + (a.ny + 2) * (base[2] + 1));
         unsigned long long small = 0;
         while (rem) {
@@ -689,61 +602,54 @@ __device__ __forceinline__ void push_body(const PartArgs &a, int blk)
                 small |= m;
                 continue;
             }
-            const float tot = wave_reduce64<FIX>(val, mine, lane);
+            const int tot = wave_reduce64(val, mine, lane);
             const int bx = __builtin_amdgcn_readlane(base[0], leader);
             const int by = __builtin_amdgcn_readlane(base[1], leader);
             const int bz = __builtin_amdgcn_readlane(base[2], leader);
-            if (lane < 54 && (FIX ? __float_as_int(tot) != 0 : tot != 0.f)) {
-                const bool inside = bx >= 0 && bx + 2 < a.nx && by >= 0 && by + 2 < a.ny && bz >= 0 &&
-                                    bz + 2 < a.nz;
-                if (FIX) {
-                    int comp = lc;
-                    const int q = inside ? (bx + a.nx * (by + a.ny * bz)) + lrel
-                                         : slot_index(a, lane, bx, by, bz, comp);
-                    if (q >= 0) add_fixed(a, comp, q, __float_as_int(tot));
-                } else {
-                    float *ad = inside ? Jl + (bx + a.nx * (by + a.ny * bz)) + lrel : slot_addr(a, lane, bx, by, bz);
-                    if (ad) gatomic_add(G(ad), tot);
-                }
+            if (lane < 54 && tot != 0) {
+                const bool inside = bx >= 0 && bx + 2 < a.nx && by >= 0 && by + 2 < a.ny && bz >= 0 && bz + 2 < a.nz;
+                int comp = lc;
+                const int q = inside ? (bx + a.nx * (by + a.ny * bz)) + lrel : slot_index(a, lane, bx, by, bz, comp);
+                if (q >= 0) add_fixed(a, comp, q, tot);
             }
+        }
+        if ((small >> lane) & 1ull)
+            lane_deposit(a, base, [&](int s) { return val[s]; },
+                         [&](int comp, int q, int u) { add_fixed(a, comp, q, u); });
+        return;
+    }
+    if (MODE == 0) {
+        __shared__ RowLds L;
+        // a lane that does not deposit leaves zeros (a factor 0 times an
+        // uninitialised value could be NaN)
+        const AxisF fy = axis_factors(y0, y1, base[1]), fz = axis_factors(z0, z1, base[2]);
+        row_factors(L, lane, fy, fz);
+        const bool yz = __ballot(fy.P[0] != 0.f || fy.P[1] != 0.f || fz.P[0] != 0.f || fz.P[1] != 0.f) != 0ull;
+        unsigned long long small = 0;
+        while (rem) {
+            const int leader = __ffsll((long long)rem) - 1;
+            // a lane behind the leader by less than a cell still joins its pass
+            const int X0 = __builtin_amdgcn_readlane(base[0], leader) - 1;
+            const int by = __builtin_amdgcn_readlane(base[1], leader);
+            const int bz = __builtin_amdgcn_readlane(base[2], leader);
+            const bool mine = ((rem >> lane) & 1ull) && base[1] == by && base[2] == bz &&
+                              (unsigned)(base[0] - X0) < (unsigned)ROW_BASES;
+            const unsigned long long m = __ballot(mine);
+            rem &= ~m;
+            if (__popcll(m) < ROW_LANES) small |= m;
+            else deposit_rows(a, L, m, mine, lane, x0, x1, X0, by, bz, yz);
         }
         rem = small;
     }
     if ((rem >> lane) & 1ull) {
-        const bool inside = base[0] >= 0 && base[0] + 2 < a.nx && base[1] >= 0 && base[1] + 2 < a.ny &&
-                            base[2] >= 0 && base[2] + 2 < a.nz;
-        if (inside) {
-            // slot offsets from the window's base node are uniform: one add per slot
-            const int lin = base[0] + a.nx * (base[1] + a.ny * base[2]);
-            const int sy = a.nx, sz = a.nx * a.ny;
-#pragma unroll
-            for (int s = 0; s < 54; ++s) {
-                int comp, oi, oj, ok;
-                slot_geom(s, comp, oi, oj, ok);
-                const float v = val[s];
-                if (FIX) {
-                    const int u = __float_as_int(v);
-                    if (u != 0) add_fixed(a, comp, lin + (oi + sy * oj + sz * ok), u);
-                } else {
-                    float *J = comp == 0 ? a.Jb[0] : (comp == 1 ? a.Jb[1] : a.Jb[2]);
-                    if (v != 0.f) gatomic_add(G(J) + lin + (oi + sy * oj + sz * ok), v);
-                }
-            }
-        } else {
-#pragma unroll
-            for (int s = 0; s < 54; ++s) {
-                const float v = val[s];
-                if (FIX) {
-                    const int u = __float_as_int(v);
-                    int comp;
-                    const int q = u != 0 ? slot_index(a, s, base[0], base[1], base[2], comp) : -1;
-                    if (q >= 0) add_fixed(a, comp, q, u);
-                } else if (v != 0.f) {
-                    float *ad = slot_addr(a, s, base[0], base[1], base[2]);
-                    if (ad) gatomic_add(G(ad), v);
-                }
-            }
-        }
+        const AxisF fx = axis_factors(x0, x1, base[0]), fy = axis_factors(y0, y1, base[1]),
+                    fz = axis_factors(z0, z1, base[2]);
+        lane_deposit(a, base, [&](int s) { return a.qd * slot_value(fx, fy, fz, s); },
+                     [&](int comp, int q, float v) {
+                         // select, not a[comp]: a runtime index into the argument block would put it in scratch
+                         float *J = comp == 0 ? a.Jb[0] : (comp == 1 ? a.Jb[1] : a.Jb[2]);
+                         gatomic_add(G(J) + q, v);
+                     });
     }
 }
 
