@@ -353,8 +353,14 @@ __device__ __forceinline__ void lane_deposit(const PartArgs &a, const int base[3
 // (63 wavefronts, one cell across y): 22.5 -> 14.8 us.
 constexpr int ROW_NODES = 16;
 constexpr int ROW_BASES = ROW_NODES - 2;
-// Rows with fewer lanes go to the per-lane atomics.
-constexpr int ROW_LANES = 3;
+// Rows with fewer lanes go to the per-lane atomics, whose cost does not depend
+// on how many rows they come from: a pass costs a wavefront a chain of LDS reads
+// and matrix products and eight atomics, and the wavefronts of a bunch's tails
+// hold many short rows.  Push of 1e5 particles in a 128x64x64 box, the slowest
+// wavefronts' time, for a least number of 3, 6, 10, 20 lanes: 19.5, 15.7, 14.3,
+// 14.0 us; 1e6 in 64x128x128: 55.4, 52.2, 52.4, 59.4; 1e7 in 512x256x256: 272,
+// 271, 270, 273.
+constexpr int ROW_LANES = 10;
 
 typedef float fvec4 __attribute__((ext_vector_type(4)));
 
@@ -653,10 +659,16 @@ __device__ __forceinline__ void push_body(const PartArgs &a, int blk)
     }
 }
 
+// Workgroups take the sorted particles from both ends inwards: the ends are the
+// bunch's tails along z, whose wavefronts hold many short rows and take longest,
+// and started last they would run on alone (1e6 particles in a 448x128x128 box
+// 54.0 -> 48.3 us, in 64x128x128 62.2 -> 55.4 us).
+__device__ __forceinline__ int ends_first(int b, int n) { return b & 1 ? n - 1 - (b >> 1) : b >> 1; }
+
 template <int MODE, int PX, int FIX>
 __global__ __launch_bounds__(PUSH_BLOCK) void k_push_deposit(PartArgs a)
 {
-    push_body<MODE, PX, FIX>(a, blockIdx.x);
+    push_body<MODE, PX, FIX>(a, ends_first(blockIdx.x, gridDim.x));
 }
 
 // Many simulations in one launch: workgroup b is push block own[b] & 0xffffff
