@@ -307,8 +307,10 @@ pic_status pic_grad_noalloc(pic_ctx *ctx, double omega0, int64_t nsteps, double 
 /* Result of the field-kernel tile autotuner. */
 typedef struct {
     int32_t tile;     /* chosen tile variant index */
-    int32_t fx, fy;   /* its cells along x and y (one z plane per workgroup) */
-    int32_t order;    /* 0: tiles numbered x, y, z (plane by plane); 1: x, z, y */
+    int32_t fx, fy;   /* its cells along x and y (one z plane per workgroup); 256 x 1:
+                         runs of 256 cells in memory order */
+    int32_t order;    /* 0: tiles numbered x, y, z (plane by plane); 1: x, z, y (for the
+                         runs: a band of 16 rows through all planes) */
     int32_t nshapes;  /* variants in the table (entries of ms) */
     double ms[16];    /* measured ms per H + E launch pair, per variant (0 when forced) */
 } pic_tune_out;
@@ -318,8 +320,9 @@ typedef struct {
  * Drude + E update) for this grid.  With force = -1, times reps H + E launch
  * pairs of every variant in the library's table on the context's stream, starting from
  * the current field state and restoring it afterwards (fields, CPML
- * memories, Drude current, step clock), and keeps the fastest (the default
- * shape 0 unless another is more than 3 % faster); with force in
+ * memories, Drude current, step clock), and keeps the fastest (the shape
+ * pic_init chose for the grid's sizes unless another is more than 3 % faster);
+ * with force in
  * [0, nshapes) selects that shape without timing.  Results of later steps
  * do not depend on the shape (each cell's arithmetic is the same).
  * Synchronises the stream.  out may be NULL.  Errors: PIC_EINVAL, PIC_ENOMEM,

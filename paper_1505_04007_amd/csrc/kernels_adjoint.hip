@@ -23,13 +23,12 @@
 
 namespace pic {
 
-__device__ __forceinline__ bool adj_tile_cell(const AdjArgs &a, int t, int &i, int &j, int &k)
+constexpr int ADJ_BLOCK = 256;
+
+__device__ __forceinline__ bool adj_cell(const AdjArgs &a, int t, int &i, int &j, int &k)
 {
-    const int bx = t % a.gx, by = (t / a.gx) % a.gy;
-    k = t / (a.gx * a.gy);
-    i = bx * FX + threadIdx.x;
-    j = by * FY + threadIdx.y;
-    return i < a.nx && j < a.ny && k < a.nz;
+    run_cell(t * ADJ_BLOCK, threadIdx.x, a.nx, a.ny, a.dx, a.dy, i, j, k);
+    return k < a.nz;
 }
 
 template <int AX>
@@ -137,10 +136,10 @@ __device__ __forceinline__ void h_prep(const AdjArgs &a, float t, int i, int j, 
 // so face m of Hx is read with + by the Ey edge at m and the Ez edge at m
 // (through their weights) and with - by the Ey edge at m + z and the Ez edge
 // at m + y; likewise for Hy and Hz.
-__global__ __launch_bounds__(FX *FY) void k_adj_face(AdjArgs a)
+__global__ __launch_bounds__(ADJ_BLOCK) void k_adj_face(AdjArgs a)
 {
     int i, j, k;
-    if (!adj_tile_cell(a, xcd_tile(), i, j, k)) return;
+    if (!adj_cell(a, xcd_tile(), i, j, k)) return;
     const int id = i + a.nx * (j + a.ny * k);
     bool okx, oky, okz;
     const int ox = nb_off(i, 1, a.nx, a.per[0], 1, okx);
@@ -201,10 +200,10 @@ __global__ __launch_bounds__(FX *FY) void k_adj_face(AdjArgs a)
     }
 }
 
-__global__ __launch_bounds__(FX *FY) void k_adj_edge(AdjArgs a)
+__global__ __launch_bounds__(ADJ_BLOCK) void k_adj_edge(AdjArgs a)
 {
     int i, j, k;
-    if (!adj_tile_cell(a, xcd_tile(), i, j, k)) return;
+    if (!adj_cell(a, xcd_tile(), i, j, k)) return;
     const int id = i + a.nx * (j + a.ny * k);
     const bool mx = e_masked<0>(a, i, j, k), my = e_masked<1>(a, i, j, k), mz = e_masked<2>(a, i, j, k);
     const float ex1 = a.Ea[0][id], ey1 = a.Ea[1][id], ez1 = a.Ea[2][id];
@@ -313,12 +312,12 @@ __global__ void k_box_copy(BoxCopyArgs a)
 
 void launch_adj_face(const AdjArgs &a, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_adj_face, dim3(field_tiles(a.nx, a.ny, a.nz)), dim3(FX, FY), 0, s, a);
+    hipLaunchKernelGGL(k_adj_face, dim3(field_tiles(a.nx, a.ny, a.nz, TILE_RUNS)), dim3(ADJ_BLOCK), 0, s, a);
 }
 
 void launch_adj_edge(const AdjArgs &a, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_adj_edge, dim3(field_tiles(a.nx, a.ny, a.nz)), dim3(FX, FY), 0, s, a);
+    hipLaunchKernelGGL(k_adj_edge, dim3(field_tiles(a.nx, a.ny, a.nz, TILE_RUNS)), dim3(ADJ_BLOCK), 0, s, a);
 }
 
 void launch_box_copy(const BoxCopyArgs &a, hipStream_t s)

@@ -1,9 +1,10 @@
 // Yee curl updates for gfx950: H update (vacuum form) and the fused Drude
 // polarization-current + E update.
 //
-// One thread per cell, one workgroup per (x, y) tile of one z plane (64 x 4
-// cells by default; the autotuner picks another shape from a fixed table per
-// grid), x fastest so a wavefront reads contiguous rows.  Each
+// One thread per cell, one workgroup per run of 256 cells in memory order or per
+// (x, y) tile of one z plane (default_tile's rule; the autotuner picks another
+// shape from a fixed table per grid), x fastest so a wavefront reads contiguous
+// rows.  Each
 // cell reads its own three old values and the three neighbour values its
 // curl needs (+x/+y/+z for H, -x/-y/-z for E); the neighbours are the own
 // values of adjacent lanes, rows and planes and are served by L1/L2, so the
@@ -267,18 +268,33 @@ __device__ __forceinline__ void e_cell(const FieldArgs &a, int par, int margin, 
 }
 
 // Decompose a tile index of one simulation into (i, j, k); false when the
-// thread lies past the grid's x / y extent.
+// thread lies past the grid's extent.
 template <int TXW, int TYW, int ZO>
 __device__ __forceinline__ bool tile_cell(const FieldArgs &a, int t, int &i, int &j, int &k)
 {
-    const int bx = t % a.gx;
+    constexpr bool runs = TXW == 256 && TYW == 1;
+    if (runs && !ZO) {
+        run_cell(t * 256, threadIdx.x, a.nx, a.ny, a.dx, a.dy, i, j, k);
+        return k < a.nz;
+    }
+    if (runs) {
+        const int r = div(t, a.dy), c = t - r * a.gx;  // run c of a band's plane
+        const int b = div(r, a.dz);
+        k = r - b * a.nz;
+        const int q = div(c * 256, a.dx);
+        i = c * 256 - q * a.nx + threadIdx.x;
+        const int row = q + step_div(i, a.nx);
+        j = b * BAND_ROWS + row;
+        return row < BAND_ROWS && j < a.ny;
+    }
+    const int r = div(t, a.dx), bx = t - r * a.gx;
     int by;
     if (ZO) {
-        k = (t / a.gx) % a.nz;
-        by = t / (a.gx * a.nz);
+        by = div(r, a.dz);
+        k = r - by * a.nz;
     } else {
-        by = (t / a.gx) % a.gy;
-        k = t / (a.gx * a.gy);
+        k = div(r, a.dy);
+        by = r - k * a.gy;
     }
     i = bx * TXW + threadIdx.x;
     j = by * TYW + threadIdx.y;

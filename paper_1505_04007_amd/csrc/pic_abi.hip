@@ -89,9 +89,7 @@ void build_args(pic_ctx *c)
     a.nx = c->n[0];
     a.ny = c->n[1];
     a.nz = c->n[2];
-    a.tile = c->tile;
-    a.gx = (c->n[0] + pic::TILE_FX[c->tile] - 1) / pic::TILE_FX[c->tile];
-    a.gy = (c->n[1] + pic::TILE_FY[c->tile] - 1) / pic::TILE_FY[c->tile];
+    pic::set_tile(a, c->tile);
     a.S = (float)c->S;
     for (int d = 0; d < 3; ++d) {
         a.per[d] = c->per[d];
@@ -487,6 +485,7 @@ static pic_status init_impl(pic_ctx *c, const pic_grid *grid, double dx, double 
         return fail(c, PIC_EINVAL, "wp_map / gamma_map must be finite and >= 0");
     c->dx = dx;
     c->dt = dt;
+    c->tile = pic::default_tile(nn[0], nn[1]);
     c->S = kC * dt / dx;
     double wpmax = 0.0;
     for (long long q = 0; q < ncell; ++q) wpmax = std::max(wpmax, wp_map[q]);

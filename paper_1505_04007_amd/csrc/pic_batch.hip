@@ -118,9 +118,7 @@ pic_status batch_upload_fields(pic_batch *b, int shape)
     for (int q = 0; q < n; ++q) {
         const pic_ctx *c = b->ctx[q];
         fa[q] = c->fa;
-        fa[q].tile = shape;
-        fa[q].gx = (c->n[0] + pic::TILE_FX[shape] - 1) / pic::TILE_FX[shape];
-        fa[q].gy = (c->n[1] + pic::TILE_FY[shape] - 1) / pic::TILE_FY[shape];
+        pic::set_tile(fa[q], shape);
         tiles[q] = pic::batch_field_units(c->n[0], c->n[1], c->n[2], shape);
         if (tiles[q] >= (1LL << 24)) return bfail(b, PIC_EINVAL, "member %d has too many field tiles for a batch", q);
     }
@@ -131,6 +129,15 @@ pic_status batch_upload_fields(pic_batch *b, int shape)
     b->tile = shape;
     b->total_tiles = (int)tab.size();
     return PIC_OK;
+}
+
+// The default shape of the members' largest plane (one shape for all).
+int batch_default_tile(const pic_batch *b)
+{
+    int t = pic::TILE_RUNS;
+    for (const pic_ctx *c : b->ctx)
+        if (pic::default_tile(c->n[0], c->n[1]) == pic::TILE_BAND_RUNS) t = pic::TILE_BAND_RUNS;
+    return t;
 }
 
 // Capture one sort period (sort_every steps, then the sorts; since_sort is 0
@@ -224,7 +231,7 @@ static pic_status batch_create_impl(pic_batch *b, pic_ctx *const *ctxs, int32_t 
         b->tiles_cap = std::max(b->tiles_cap, (size_t)t);
     }
     BHIP(b, hipMalloc(&b->d_tiles, sizeof(int) * std::max<size_t>(b->tiles_cap, 1)));
-    pic_status st = batch_upload_fields(b, 0);
+    pic_status st = batch_upload_fields(b, batch_default_tile(b));
     if (st != PIC_OK) return st;
     BHIP(b, hipMemcpy(b->d_pa, pa.data(), sizeof(pic::PartArgs) * n, hipMemcpyHostToDevice));
     BHIP(b, hipMemcpy(b->d_pr, pr.data(), sizeof(pic::ProbeArgs) * n, hipMemcpyHostToDevice));
@@ -352,7 +359,7 @@ pic_status pic_batch_tune(pic_batch *b, int32_t reps, int32_t force, pic_tune_ou
         (void)hipStreamSynchronize(b->ext);
         for (void *p : saved) (void)hipFree(p);
         if (st != PIC_OK) return st;
-        best = pick_shape(res.ms);
+        best = pick_shape(res.ms, batch_default_tile(b));
     }
     pic_status st = batch_upload_fields(b, best);
     if (st != PIC_OK) return st;

@@ -105,15 +105,15 @@ pic_status ckpt_load(pic_ctx *c, const char *src, const Mirror &m)
     return PIC_OK;
 }
 
-// The fastest shape; the default one unless another beats it by more than
-// 3 % (isolated H + E timings do not see the particle kernels' cache traffic
+// The fastest shape; the grid's default one unless another beats it by more
+// than 3 % (isolated H + E timings do not see the particle kernels' cache traffic
 // between them, so small margins do not carry over to whole steps).
-int pick_shape(const double *ms)
+int pick_shape(const double *ms, int def)
 {
     int best = 0;
     for (int v = 1; v < pic::N_TILE_SHAPES; ++v)
         if (ms[v] < ms[best]) best = v;
-    return ms[best] < 0.97 * ms[0] ? best : 0;
+    return ms[best] < 0.97 * ms[def] ? best : def;
 }
 
 }  // namespace pich
@@ -297,8 +297,8 @@ pic_status grad_impl(pic_ctx *c, GradScratch &g, double omega0, long long N, lon
     aa.nx = c->n[0];
     aa.ny = c->n[1];
     aa.nz = c->n[2];
-    aa.gx = (c->n[0] + pic::FX - 1) / pic::FX;  // the adjoint kernels use the default tile
-    aa.gy = (c->n[1] + pic::FY - 1) / pic::FY;
+    aa.dx = pic::make_div(c->n[0]);
+    aa.dy = pic::make_div(c->n[1]);
     aa.S = (float)c->S;
     for (int d = 0; d < 3; ++d) {
         aa.per[d] = c->per[d];
@@ -459,9 +459,7 @@ pic_status tune_fields(pic_ctx *c, int reps, double *ms)
     pic_status st = PIC_OK;
     for (int v = 0; v < pic::N_TILE_SHAPES && st == PIC_OK; ++v) {
         pic::FieldArgs f = c->fa;
-        f.tile = v;
-        f.gx = (c->n[0] + pic::TILE_FX[v] - 1) / pic::TILE_FX[v];
-        f.gy = (c->n[1] + pic::TILE_FY[v] - 1) / pic::TILE_FY[v];
+        pic::set_tile(f, v);
         pic::launch_h_update(f, c->stream);
         pic::launch_e_update(f, c->stream);
         (void)hipEventRecord(e0, c->stream);
@@ -565,7 +563,7 @@ pic_status pic_tune(pic_ctx *c, int32_t reps, int32_t force, pic_tune_out *out)
         HIP_TRY(c, hipStreamSynchronize(c->stream));
         pic_status st = tune_fields(c, reps, res.ms);
         if (st != PIC_OK) return st;
-        c->tile = pick_shape(res.ms);
+        c->tile = pick_shape(res.ms, pic::default_tile(c->n[0], c->n[1]));
     }
     build_args(c);
     res.tile = c->tile;

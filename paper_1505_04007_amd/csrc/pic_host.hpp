@@ -230,7 +230,7 @@ pic_status ckpt_save(pic_ctx *c, char *dst, Mirror &m);
 pic_status ckpt_load(pic_ctx *c, const char *src, const Mirror &m);
 
 // The tuners' choice among timed shapes (pic_grad.hip).
-int pick_shape(const double *ms);
+int pick_shape(const double *ms, int def);
 
 // Bind this device's address of the static gradient scratch to the context
 // (pic_grad.hip; called by pic_init with the context's device current).  A

@@ -20,6 +20,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
+
 namespace pic {
 
 constexpr int PBLOCK = 256;  // particle sort kernels
@@ -28,18 +30,40 @@ constexpr int PBLOCK = 256;  // particle sort kernels
 // compute unit is freed only when its last wavefront ends, so single-wave
 // workgroups keep the units fuller (8 % faster than 256 threads).
 constexpr int PUSH_BLOCK = 64;
-constexpr int FX = 64;       // default field tile: 64 x 4 cells of one z plane
-constexpr int FY = 4;
 
 // Field-kernel tile shapes (cells along x, y of one z plane per workgroup)
-// and tile orders the autotuner chooses from; shape 0 is the default.
+// and tile orders the autotuner chooses from.
 // Order 0 numbers tiles x, then y, then z (a plane at a time); order 1 x,
 // then z, then y (a band of rows marches through all planes, so the next
-// plane's values are still in L2 when its tiles run).
+// plane's values are still in L2 when its tiles run).  The 256 x 1 shapes take
+// runs of 256 cells in memory order, across the ends of rows (order 0: of the
+// whole grid; order 1: of a band of BAND_ROWS rows of a plane).
 constexpr int N_TILE_SHAPES = 16;
 constexpr int TILE_FX[N_TILE_SHAPES] = {64, 64, 128, 256, 32, 64, 128, 32, 64, 64, 128, 256, 32, 64, 128, 32};
 constexpr int TILE_FY[N_TILE_SHAPES] = {4, 2, 2, 1, 8, 8, 4, 4, 4, 2, 2, 1, 8, 8, 4, 4};
 constexpr int TILE_ZO[N_TILE_SHAPES] = {0, 0, 0, 0, 0, 0, 0, 0, 1, 1, 1, 1, 1, 1, 1, 1};
+constexpr int TILE_RUNS = 3, TILE_BAND_RUNS = 11;
+// Rows of a band: enough that the rows re-read from the next band are few, few
+// enough that a band's plane (nx x 16 cells) is still in an XCD's L2 when the
+// next plane's run needs it.  H + E launch pair on 512x256x256 cells: 4, 8, 16
+// rows 563, 561, 556 us; 240x96x96: 44.8, 44.7, 41.5 us.
+constexpr int BAND_ROWS = 16;
+
+// Division of 0 <= n < 2^31 by a fixed d >= 1: n / d = n m >> s with
+// s = 31 + ceil(log2 d), m = floor(2^s / d) + 1 < 2^32 (m d = 2^s + e with
+// 0 < e <= d, so n m / 2^s exceeds n / d by n e / (d 2^s) < 1 / d).
+struct Div {
+    unsigned m;
+    int s;
+};
+inline Div make_div(int d)
+{
+    int l = 0;
+    while ((1ll << l) < d) ++l;
+    return {(unsigned)(((1ull << (31 + l)) / (unsigned)d) + 1), 31 + l};
+}
+__device__ __forceinline__ int div(int n, Div d) { return (int)(((unsigned long long)(unsigned)n * d.m) >> d.s); }
+
 // A batched field launch gives each workgroup this many consecutive tiles of
 // one member.  One: a workgroup's tiles run one after another (the next
 // tile's loads wait for the last one's stores, which may alias them as far
@@ -77,7 +101,9 @@ struct PmlAxis {
 struct FieldArgs {
     int nx, ny, nz;
     int tile;    // tile shape index (TILE_FX / TILE_FY)
-    int gx, gy;  // tiles along x and y
+    int gx, gy;  // tiles along x and y (TILE_BAND_RUNS: runs per band and plane, bands)
+    Div dx, dy;     // division by nx and ny (the 256 x 1 shapes), else by gx and by gy
+    Div dz;         // by nz
     int per[3];
     float S;
     float *E[3];
@@ -205,16 +231,69 @@ __device__ __forceinline__ int box_margin(int since_sort, float S)
     return 3 + (int)ceilf((float)(since_sort + 1) * S);
 }
 
+// Tiles along x and y of a shape, and the workgroups of a field launch.
+inline void tile_grid(int nx, int ny, int shape, int &gx, int &gy)
+{
+    const bool band = shape == TILE_BAND_RUNS;
+    gx = band ? (int)(((long long)nx * std::min(BAND_ROWS, ny) + 255) / 256) : (nx + TILE_FX[shape] - 1) / TILE_FX[shape];
+    gy = band ? (ny + BAND_ROWS - 1) / BAND_ROWS : (ny + TILE_FY[shape] - 1) / TILE_FY[shape];
+}
+
 inline int field_tiles(int nx, int ny, int nz, int shape = 0)
 {
-    const int fx = TILE_FX[shape], fy = TILE_FY[shape];
-    return ((nx + fx - 1) / fx) * ((ny + fy - 1) / fy) * nz;
+    if (shape == TILE_RUNS) return (int)(((long long)nx * ny * nz + 255) / 256);
+    int gx, gy;
+    tile_grid(nx, ny, shape, gx, gy);
+    return gx * gy * nz;
+}
+
+// The shape a grid gets before any tuning.  Runs of memory order leave no lane
+// idle at the ends of rows and load aligned; they go through the grid plane by
+// plane up to 2^15 cells a plane and band by band above, where a plane (36 bytes
+// a cell and kernel) would no longer stay in L2 until the next needs it.  H + E
+// launch pair, plane runs / band runs / 64 x 4 cells: 281x1x3601 cells 23.3 /
+// 29.2 / 29.3 us, 91x45x53 7.7 / 10.0 / 8.3, 208x80x80 28.8 / 28.2 / 35.0,
+// 448x128x128 125.7 / 114.3 / 126.1, 512x256x256 591 / 556 / 615.
+inline int default_tile(int nx, int ny) { return (long long)nx * ny > (1 << 15) ? TILE_BAND_RUNS : TILE_RUNS; }
+
+inline void set_tile(FieldArgs &a, int shape)
+{
+    a.tile = shape;
+    tile_grid(a.nx, a.ny, shape, a.gx, a.gy);
+    const bool runs = shape == TILE_RUNS, band = shape == TILE_BAND_RUNS;
+    a.dx = make_div(runs || band ? a.nx : a.gx);
+    a.dy = make_div(runs ? a.ny : band ? a.gx : a.gy);
+    a.dz = make_div(a.nz);
 }
 
 // Work units of one member in a batched field launch.
 inline long long batch_field_units(int nx, int ny, int nz, int shape)
 {
     return ((long long)field_tiles(nx, ny, nz, shape) + BATCH_TILES - 1) / BATCH_TILES;
+}
+
+// Quotient and remainder of a small step past a row's (or plane's) start:
+// q, r of 0 <= n < d + 256 by d.
+__device__ __forceinline__ int step_div(int &n, int d)
+{
+    int q;
+    if (d >= 256) {
+        q = n >= d ? 1 : 0;
+    } else {
+        // n < 511: (n + 1/2) / d is at least 1 / (2 d) off an integer
+        q = (int)(((float)n + 0.5f) * (1.f / (float)d));
+    }
+    n -= q * d;
+    return q;
+}
+
+// Cell tid of the run of cells starting at c: (i, j, k) in memory order.
+__device__ __forceinline__ void run_cell(int c, int tid, int nx, int ny, Div dx, Div dy, int &i, int &j, int &k)
+{
+    const int r = div(c, dx), k0 = div(r, dy);
+    i = c - r * nx + tid;
+    j = r - k0 * ny + step_div(i, nx);
+    k = k0 + step_div(j, ny);
 }
 
 // Linear offset to the neighbour at distance d = +-1 along an axis of n
@@ -312,7 +391,7 @@ void launch_probe_batch(const ProbeArgs *args, int n, hipStream_t s);
 // difference.
 struct AdjArgs {
     int nx, ny, nz;
-    int gx, gy;
+    Div dx, dy;  // division by nx and ny: one thread per cell, in memory order
     int per[3];
     float S;
     float *Ea[3];
