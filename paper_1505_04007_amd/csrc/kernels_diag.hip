@@ -3,50 +3,37 @@
 
 namespace pic {
 
-// F_p(w_m) += dt Ez_p^n exp(-i w_m n dt) for the E^n just computed (Sec. IV,
-// Figs. 6-7: Ez at the film surface and its spectrum).  The phase is
-// evaluated directly in FP64 each step.
-// The last kernel of a step: after sampling, it advances the step clock
-// (H parity, steps since the sort, step number) for the next step.
-__device__ __forceinline__ void probe_body(const ProbeArgs &a)
+constexpr int PROBE_BLOCK = 256;
+
+__global__ __launch_bounds__(PROBE_BLOCK) void k_probe(ProbeArgs a, int advance)
 {
-    const int t = threadIdx.x;
     const gp<DevState> st = G(a.st);
-    const gp<const float> Ez = G(a.Ez);
-    const gp<const int> pidx = G(a.pidx);
-    const long long n1 = st->step + 1;  // E^{n+1} was just computed
-    const double tn = (double)n1 * a.dt;
-    for (int q = t; q < a.nprobe * a.nfreq; q += blockDim.x) {
-        const int p = q / a.nfreq, f = q - p * a.nfreq;
-        const double ez = (double)Ez[pidx[p]];
-        double sn, cs;
-        sincos(G(a.omega)[f] * tn, &sn, &cs);
-        G(a.fre)[q] += a.dt * ez * cs;
-        G(a.fim)[q] -= a.dt * ez * sn;
-    }
-    if (a.series && t < a.nprobe && n1 - 1 < a.series_len)
-        G(a.series)[(n1 - 1) * a.nprobe + t] = Ez[pidx[t]];
-    if (a.gser && t < a.nprobe && n1 > a.g0 && n1 <= a.g0 + a.gn)
-        G(a.gser)[(n1 - a.g0 - 1) * a.nprobe + t] = (double)Ez[pidx[t]];
+    const long long n1 = st->step + advance;
+    probe_dft(a, n1, threadIdx.x, PROBE_BLOCK);
+    if (!advance) return;
     __syncthreads();  // every thread has read the clock before it moves
-    if (t == 0) {
+    if (threadIdx.x == 0) {
         st->parity ^= 1;
         st->since_sort += 1;
         st->step = n1;
     }
 }
-__global__ void k_probe(ProbeArgs a) { probe_body(a); }
 
-__global__ void k_probe_batch(const ProbeArgs *args) { probe_body(args[blockIdx.x]); }
-
-void launch_probe(const ProbeArgs &a, hipStream_t s)
+__global__ __launch_bounds__(PROBE_BLOCK) void k_probe_batch(const ProbeArgs *args)
 {
-    hipLaunchKernelGGL(k_probe, dim3(1), dim3(256), 0, s, a);
+    const ProbeArgs &a = args[blockIdx.x];
+    probe_dft(a, G(a.st)->step, threadIdx.x, PROBE_BLOCK);
+}
+
+void launch_probe(const ProbeArgs &a, bool advance, hipStream_t s)
+{
+    if (a.nprobe <= 0 && !advance) return;
+    hipLaunchKernelGGL(k_probe, dim3(1), dim3(PROBE_BLOCK), 0, s, a, advance ? 1 : 0);
 }
 
 void launch_probe_batch(const ProbeArgs *args, int n, hipStream_t s)
 {
-    if (n > 0) hipLaunchKernelGGL(k_probe_batch, dim3(n), dim3(256), 0, s, args);
+    if (n > 0) hipLaunchKernelGGL(k_probe_batch, dim3(n), dim3(PROBE_BLOCK), 0, s, args);
 }
 
 // Node-centred cloud-in-cell charge density in FP64 (nodes (nx+1)(ny+1)(nz+1)).

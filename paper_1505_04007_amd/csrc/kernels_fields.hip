@@ -301,11 +301,48 @@ __device__ __forceinline__ bool tile_cell(const FieldArgs &a, int t, int &i, int
     return i < a.nx && j < a.ny && k < a.nz;
 }
 
-template <int TXW, int TYW, int ZO>
-__global__ __launch_bounds__(TXW *TYW) void k_h_update(FieldArgs a)
+// The E update's first workgroup moves the clock (DevState) to the next step.
+// After the cells' work: uniform loads behind a store (the layers' tables, the
+// particle box) are no longer scalar loads to the compiler, which cost 15 % of a
+// kernel.
+__device__ __forceinline__ void e_tick(const FieldArgs &a, int parity, int since)
 {
+    if (!a.tick) return;
+    const gp<DevState> st = G(a.st);
+    st->parity = parity ^ 1;
+    st->since_sort = since + 1;
+    st->step += 1;
+}
+
+__device__ __forceinline__ bool first_thread() { return threadIdx.x == 0 && threadIdx.y == 0; }
+
+// Workgroups in front of an H update's tiles: the first (of each simulation of a
+// batch) passes the step's clock to the E update and, with pr.nprobe > 0, takes
+// the probes of the step before; a whole round of the XCDs, so that the tiles
+// keep theirs.
+constexpr int XCDS = 8;
+
+__device__ __forceinline__ void h_front(const ProbeArgs &pr, DevState *state, int t, int nt)
+{
+    const gp<DevState> st = G(state);
+    if (pr.nprobe > 0) probe_dft(pr, st->step, t, nt);
+    if (t == 0) {
+        st->e_parity = st->parity;
+        st->e_since = st->since_sort;
+    }
+}
+
+// FRONT: the workgroups in front (0 or XCDS).
+template <int TXW, int TYW, int ZO, int FRONT>
+__global__ __launch_bounds__(TXW *TYW) void k_h_update(FieldArgs a, ProbeArgs pr)
+{
+    const int blk = (int)blockIdx.x - FRONT;
+    if (FRONT && blk < 0) {
+        if (blockIdx.x == 0) h_front(pr, a.st, threadIdx.x + TXW * threadIdx.y, TXW * TYW);
+        return;
+    }
     int i, j, k;
-    if (!tile_cell<TXW, TYW, ZO>(a, xcd_tile(), i, j, k)) return;
+    if (!tile_cell<TXW, TYW, ZO>(a, xcd_tile(blk, gridDim.x - FRONT), i, j, k)) return;
     const gp<const DevState> st = G(a.st);
     h_cell(a, st->parity, box_margin(st->since_sort, a.S), i, j, k);
 }
@@ -314,9 +351,11 @@ template <int TXW, int TYW, int ZO>
 __global__ __launch_bounds__(TXW *TYW) void k_e_update(FieldArgs a)
 {
     int i, j, k;
-    if (!tile_cell<TXW, TYW, ZO>(a, xcd_tile_rev(), i, j, k)) return;
+    const bool in = tile_cell<TXW, TYW, ZO>(a, xcd_tile_rev(), i, j, k);
     const gp<const DevState> st = G(a.st);
-    e_cell(a, st->parity, box_margin(st->since_sort, a.S), i, j, k);
+    const int parity = a.tick ? st->e_parity : st->parity, since = a.tick ? st->e_since : st->since_sort;
+    if (in) e_cell(a, parity, box_margin(since, a.S), i, j, k);
+    if (blockIdx.x == 0 && first_thread()) e_tick(a, parity, since);
 }
 
 // Work unit u of a batched launch belongs to simulation own[u] >> 24 as its
@@ -325,9 +364,16 @@ __global__ __launch_bounds__(TXW *TYW) void k_e_update(FieldArgs a)
 // simulation's tiles BATCH_TILES * unit onwards, x-neighbours first.
 template <int TXW, int TYW, int ZO>
 __global__ __launch_bounds__(TXW *TYW) void k_h_update_batch(const FieldArgs *__restrict__ args,
-                                                             const int *__restrict__ own)
+                                                             const int *__restrict__ own,
+                                                             const ProbeArgs *__restrict__ probe, int nmem, int extra)
 {
-    const int o = own[xcd_tile()];
+    const int blk = (int)blockIdx.x - extra;
+    if (blk < 0) {
+        const int m = blockIdx.x, t = threadIdx.x + TXW * threadIdx.y;
+        if (m < nmem) h_front(probe ? probe[m] : ProbeArgs{}, args[m].st, t, TXW * TYW);
+        return;
+    }
+    const int o = own[xcd_tile(blk, gridDim.x - extra)];
     const FieldArgs &a = args[o >> 24];
     const gp<const DevState> st = G(a.st);
     const int parity = st->parity, margin = box_margin(st->since_sort, a.S);
@@ -345,12 +391,14 @@ __global__ __launch_bounds__(TXW *TYW) void k_e_update_batch(const FieldArgs *__
     const int o = own[xcd_tile_rev()];
     const FieldArgs &a = args[o >> 24];
     const gp<const DevState> st = G(a.st);
-    const int parity = st->parity, margin = box_margin(st->since_sort, a.S);
+    const int parity = a.tick ? st->e_parity : st->parity, since = a.tick ? st->e_since : st->since_sort;
+    const int margin = box_margin(since, a.S);
     const int t0 = (o & 0xffffff) * BATCH_TILES, nt = a.gx * a.gy * a.nz;
     for (int q = 0; q < BATCH_TILES && t0 + q < nt; ++q) {
         int i, j, k;
         if (tile_cell<TXW, TYW, ZO>(a, t0 + q, i, j, k)) e_cell(a, parity, margin, i, j, k);
     }
+    if ((o & 0xffffff) == 0 && first_thread()) e_tick(a, parity, since);
 }
 
 // One launch of a tile-shape instantiation: the shape index selects the
@@ -373,9 +421,12 @@ void launch_shape(int shape, int blocks, hipStream_t s, Args... args)
 
 template <int TXW, int TYW, int ZO>
 struct HLaunch {
-    static void launch(int blocks, hipStream_t s, FieldArgs a)
+    static void launch(int blocks, hipStream_t s, FieldArgs a, ProbeArgs pr)
     {
-        hipLaunchKernelGGL((k_h_update<TXW, TYW, ZO>), dim3(blocks), dim3(TXW, TYW), 0, s, a);
+        if (a.tick)
+            hipLaunchKernelGGL((k_h_update<TXW, TYW, ZO, XCDS>), dim3(blocks + XCDS), dim3(TXW, TYW), 0, s, a, pr);
+        else
+            hipLaunchKernelGGL((k_h_update<TXW, TYW, ZO, 0>), dim3(blocks), dim3(TXW, TYW), 0, s, a, pr);
     }
 };
 template <int TXW, int TYW, int ZO>
@@ -387,9 +438,11 @@ struct ELaunch {
 };
 template <int TXW, int TYW, int ZO>
 struct HBatchLaunch {
-    static void launch(int blocks, hipStream_t s, const FieldArgs *args, const int *own)
+    static void launch(int blocks, hipStream_t s, const FieldArgs *args, const int *own, const ProbeArgs *probe,
+                       int nmem, int extra)
     {
-        hipLaunchKernelGGL((k_h_update_batch<TXW, TYW, ZO>), dim3(blocks), dim3(TXW, TYW), 0, s, args, own);
+        hipLaunchKernelGGL((k_h_update_batch<TXW, TYW, ZO>), dim3(blocks), dim3(TXW, TYW), 0, s, args, own, probe,
+                           nmem, extra);
     }
 };
 template <int TXW, int TYW, int ZO>
@@ -400,9 +453,9 @@ struct EBatchLaunch {
     }
 };
 
-void launch_h_update(const FieldArgs &a, hipStream_t s)
+void launch_h_update(const FieldArgs &a, const ProbeArgs *probe, hipStream_t s)
 {
-    launch_shape<HLaunch>(a.tile, field_tiles(a.nx, a.ny, a.nz, a.tile), s, a);
+    launch_shape<HLaunch>(a.tile, field_tiles(a.nx, a.ny, a.nz, a.tile), s, a, probe ? *probe : ProbeArgs{});
 }
 
 void launch_e_update(const FieldArgs &a, hipStream_t s)
@@ -410,9 +463,11 @@ void launch_e_update(const FieldArgs &a, hipStream_t s)
     launch_shape<ELaunch>(a.tile, field_tiles(a.nx, a.ny, a.nz, a.tile), s, a);
 }
 
-void launch_h_update_batch(const FieldArgs *args, const int *own, int total, int shape, hipStream_t s)
+void launch_h_update_batch(const FieldArgs *args, const int *own, int total, int shape, const ProbeArgs *probe,
+                           int nmem, hipStream_t s)
 {
-    launch_shape<HBatchLaunch>(shape, total, s, args, own);
+    const int extra = (nmem + XCDS - 1) / XCDS * XCDS;
+    launch_shape<HBatchLaunch>(shape, total + extra, s, args, own, probe, nmem, extra);
 }
 
 void launch_e_update_batch(const FieldArgs *args, const int *own, int total, int shape, hipStream_t s)

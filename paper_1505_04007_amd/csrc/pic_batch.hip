@@ -65,16 +65,19 @@ void batch_free(pic_batch *b)
         if (q) (void)hipFree(q);
 }
 
-// The four batched launches of one step (sorts are issued separately).
-void batch_launches(pic_batch *b)
+// The batched launches of one step (sorts are issued separately).  The H update
+// carries the probes of the step before it unless that was another call's
+// (first); the last step's are a launch of their own (batch_probe).
+void batch_launches(pic_batch *b, bool first)
 {
     const int n = (int)b->ctx.size();
-    pic::launch_h_update_batch(b->d_fa, b->d_tiles, b->total_tiles, b->tile, b->stream);
+    pic::launch_h_update_batch(b->d_fa, b->d_tiles, b->total_tiles, b->tile, first ? nullptr : b->d_pr, n, b->stream);
     if (b->particles)
         pic::launch_push_deposit_batch(b->d_pa, b->d_pblocks, b->total_pblocks, b->push_mode, b->stream);
     pic::launch_e_update_batch(b->d_fa, b->d_tiles, b->total_tiles, b->tile, b->stream);
-    pic::launch_probe_batch(b->d_pr, n, b->stream);
 }
+
+void batch_probe(pic_batch *b) { pic::launch_probe_batch(b->d_pr, (int)b->ctx.size(), b->stream); }
 
 void batch_mirror_step(pic_batch *b)
 {
@@ -110,7 +113,7 @@ std::vector<int> unit_table(const std::vector<long long> &counts)
 
 // Field argument blocks of every member for tile shape `shape`, and the
 // field launches' work-unit table (re-made when the tuner changes the shape).
-pic_status batch_upload_fields(pic_batch *b, int shape)
+pic_status batch_upload_fields(pic_batch *b, int shape, bool tick = true)
 {
     const int n = (int)b->ctx.size();
     std::vector<pic::FieldArgs> fa(n);
@@ -119,6 +122,7 @@ pic_status batch_upload_fields(pic_batch *b, int shape)
         const pic_ctx *c = b->ctx[q];
         fa[q] = c->fa;
         pic::set_tile(fa[q], shape);
+        fa[q].tick = tick;
         tiles[q] = pic::batch_field_units(c->n[0], c->n[1], c->n[2], shape);
         if (tiles[q] >= (1LL << 24)) return bfail(b, PIC_EINVAL, "member %d has too many field tiles for a batch", q);
     }
@@ -152,7 +156,8 @@ pic_status batch_capture(pic_batch *b)
     BHIP(b, hipStreamSynchronize(b->ext));
     BHIP(b, hipStreamSynchronize(b->stream));
     BHIP(b, hipStreamBeginCapture(b->stream, hipStreamCaptureModeThreadLocal));
-    for (int s2 = 0; s2 < b->graph_steps; ++s2) batch_launches(b);
+    for (int s2 = 0; s2 < b->graph_steps; ++s2) batch_launches(b, s2 == 0);
+    batch_probe(b);
     // every member with particles is due at the end of the period: all their
     // sorts in one launch per kernel
     if (b->particles && b->sort_every > 0)
@@ -273,11 +278,14 @@ pic_status pic_batch_step(pic_batch *b, int64_t nsteps)
     // order the batch's stream after, and the members' stream behind, this work
     BHIP(b, hipEventRecord(b->ev_in, b->ext));
     BHIP(b, hipStreamWaitEvent(b->stream, b->ev_in, 0));
+    bool due = false;  // the last step's probes wait for the next H update
     while (nsteps > 0) {
         bool aligned = true;
         for (pic_ctx *c : b->ctx)
             aligned = aligned && (c->np == 0 || c->sort_every == 0 || c->since_sort == 0);
         if (b->use_graph && aligned && nsteps >= b->graph_steps) {
+            if (due) batch_probe(b);
+            due = false;
             BHIP(b, hipGraphLaunch(b->exec, b->stream));
             for (int s2 = 0; s2 < b->graph_steps; ++s2) batch_mirror_step(b);
             if (b->particles && b->sort_every > 0)
@@ -291,11 +299,13 @@ pic_status pic_batch_step(pic_batch *b, int64_t nsteps)
         }
         pic_status st = batch_sorts(b, true);
         if (st != PIC_OK) return st;
-        batch_launches(b);
+        batch_launches(b, !due);
+        due = true;
         BHIP(b, hipGetLastError());
         batch_mirror_step(b);
         --nsteps;
     }
+    if (due) batch_probe(b);
     BHIP(b, hipEventRecord(b->ev_out, b->stream));
     BHIP(b, hipStreamWaitEvent(b->ext, b->ev_out, 0));
     return PIC_OK;
@@ -334,13 +344,13 @@ pic_status pic_batch_tune(pic_batch *b, int32_t reps, int32_t force, pic_tune_ou
             st = bfail(b, PIC_EDEVICE, "hipEventCreate failed");
         if (st == PIC_OK && hipStreamSynchronize(b->ext) != hipSuccess) st = bfail(b, PIC_EDEVICE, "sync failed");
         for (int v = 0; v < pic::N_TILE_SHAPES && st == PIC_OK; ++v) {
-            st = batch_upload_fields(b, v);
+            st = batch_upload_fields(b, v, false);  // the clock stands still while launches are timed
             if (st != PIC_OK) break;
-            pic::launch_h_update_batch(b->d_fa, b->d_tiles, b->total_tiles, v, b->stream);
+            pic::launch_h_update_batch(b->d_fa, b->d_tiles, b->total_tiles, v, nullptr, (int)b->ctx.size(), b->stream);
             pic::launch_e_update_batch(b->d_fa, b->d_tiles, b->total_tiles, v, b->stream);
             (void)hipEventRecord(e0, b->stream);
             for (int r = 0; r < reps; ++r) {
-                pic::launch_h_update_batch(b->d_fa, b->d_tiles, b->total_tiles, v, b->stream);
+                pic::launch_h_update_batch(b->d_fa, b->d_tiles, b->total_tiles, v, nullptr, (int)b->ctx.size(), b->stream);
                 pic::launch_e_update_batch(b->d_fa, b->d_tiles, b->total_tiles, v, b->stream);
             }
             (void)hipEventRecord(e1, b->stream);

@@ -245,8 +245,10 @@ pic_status grad_impl(pic_ctx *c, GradScratch &g, double omega0, long long N, lon
         ra.to_grid = 0;
         st = step_body(c, cnt ? &ra : nullptr);
     }
+    const pic_status fin = probe_finish(c);
     c->pr = prs;
     TRY(st);
+    TRY(fin);
     {
         int flag = 0;
         HIP_TRY(c, hipMemcpyAsync(&flag, c->d_nan, 4, hipMemcpyDeviceToHost, c->stream));
@@ -333,9 +335,10 @@ pic_status grad_impl(pic_ctx *c, GradScratch &g, double omega0, long long N, lon
     aa.pidx = c->pidx;
 
     // replay: fields only, bunch current from the record, E update reading
-    // and clearing it over the whole grid, probes not accumulated
+    // and clearing it over the whole grid; no probes, the updates move the clock
     int *dfull = nullptr;
     pic::FieldArgs fr = c->fa;
+    fr.tick = 1;
     for (int d = 0; d < 3; ++d) fr.Havg[d] = nullptr;
     if (c->np > 0) {
         const int full[6] = {0, 0, 0, c->n[0] - 1, c->n[1] - 1, c->n[2] - 1};
@@ -344,11 +347,6 @@ pic_status grad_impl(pic_ctx *c, GradScratch &g, double omega0, long long N, lon
         HIP_TRY(c, hipStreamSynchronize(c->stream));
         fr.pbox = dfull;
     }
-    pic::ProbeArgs pq = c->pr;
-    pq.nprobe = 0;
-    pq.nfreq = 0;
-    pq.series = nullptr;
-    pq.gser = nullptr;
 
     // dL/dE^{s0+N} and the CPML weights of the last step's E update
     aa.mode = 2;
@@ -360,7 +358,7 @@ pic_status grad_impl(pic_ctx *c, GradScratch &g, double omega0, long long N, lon
         if (!store_all) TRY(ckpt_load(c, ck + (size_t)j * ckb, mir[(size_t)j]));
         for (long long r = a0; r < b0 && !store_all; ++r) {
             fr.snap = c->has_metal ? traj + (size_t)(r - a0) * 6 * c->nbox : nullptr;
-            pic::launch_h_update(fr, c->stream);
+            pic::launch_h_update(fr, nullptr, c->stream);
             const JbRecord &R = rec[(size_t)r];
             if (c->np > 0 && R.p) {
                 pic::BoxCopyArgs sa{};
@@ -376,7 +374,6 @@ pic_status grad_impl(pic_ctx *c, GradScratch &g, double omega0, long long N, lon
                 pic::launch_box_copy(sa, c->stream);
             }
             pic::launch_e_update(fr, c->stream);
-            pic::launch_probe(pq, c->stream);
             c->hcur = 1 - c->hcur;
             c->step++;
             c->since_sort++;
@@ -460,11 +457,12 @@ pic_status tune_fields(pic_ctx *c, int reps, double *ms)
     for (int v = 0; v < pic::N_TILE_SHAPES && st == PIC_OK; ++v) {
         pic::FieldArgs f = c->fa;
         pic::set_tile(f, v);
-        pic::launch_h_update(f, c->stream);
+        f.tick = 0;  // the clock stands still while launches are timed
+        pic::launch_h_update(f, nullptr, c->stream);
         pic::launch_e_update(f, c->stream);
         (void)hipEventRecord(e0, c->stream);
         for (int r = 0; r < reps; ++r) {
-            pic::launch_h_update(f, c->stream);
+            pic::launch_h_update(f, nullptr, c->stream);
             pic::launch_e_update(f, c->stream);
         }
         (void)hipEventRecord(e1, c->stream);

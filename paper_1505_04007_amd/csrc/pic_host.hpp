@@ -88,6 +88,7 @@ struct pic_ctx {
     bool timed_now = false;  // the launch being issued has a start event
 
     long long step = 0;
+    bool probe_due = false;  // the last step's probes wait for the next H update (or the call's end)
     int tile = 0;  // field-kernel tile shape (pic_tune)
     int sort_every = 0, check_every = 0;
     long long since_sort = 0;
@@ -166,6 +167,7 @@ void tstop(pic_ctx *c, int fam);
 pic_status do_sort(pic_ctx *c);
 pic_status step_body(pic_ctx *c, const pic::BoxCopyArgs *rec);
 pic_status step_once(pic_ctx *c);
+pic_status probe_finish(pic_ctx *c);
 pic::DiagArgs diag_args(pic_ctx *c);
 
 inline size_t align256(size_t b) { return (b + 255) & ~(size_t)255; }

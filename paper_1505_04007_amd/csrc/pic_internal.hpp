@@ -71,12 +71,20 @@ __device__ __forceinline__ int div(int n, Div d) { return (int)(((unsigned long 
 // table, argument block, device state) it would share.
 constexpr int BATCH_TILES = 1;
 
+// The clock of a step.  Every workgroup of its two field updates reads it.  The
+// probe launch at the step's end moves it; or (FieldArgs::tick) the field updates
+// do by themselves, and no launch is spent on it: the H update reads (parity,
+// since_sort), one extra workgroup of it copies them to (e_parity, e_since), the
+// E update reads those and its first workgroup writes the next step's (parity,
+// since_sort) and step.
 struct DevState {
     int parity;      // H[parity] holds H^{n-1/2} at the start of step n
     int since_sort;  // steps since the last cell sort
+    int e_parity;    // with tick: the same for the step's E update
+    int e_since;
     int pcur;        // particle buffer set in use
     int pad;
-    long long step;  // steps taken
+    long long step;  // steps taken: E^step is in memory
     float *P[6];     // set pcur's arrays (x, y, z, ux, uy, uz), written with pcur by the sort
 };
 
@@ -123,6 +131,7 @@ struct FieldArgs {
     double qinv;                // V/m per fixed-point unit
     const int *pbox;  // device [6]: lo x,y,z, hi x,y,z (cells, inclusive), or null
     int *nan_flag;
+    int tick;         // the field updates move the clock (0: the probe launch does, or nothing)
     DevState *st;
 };
 
@@ -333,15 +342,15 @@ __device__ __forceinline__ void gatomic_add(gp<unsigned long long> p, unsigned l
     __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Workgroup -> tile with XCD locality: the 8 XCDs receive workgroups round
-// robin, so workgroup b runs on XCD b % 8; give each XCD a contiguous block
-// of tiles.
-__device__ __forceinline__ int xcd_tile()
+// Workgroup b of B -> tile with XCD locality: the 8 XCDs receive workgroups
+// round robin, so workgroup b runs on XCD b % 8; give each XCD a contiguous
+// block of tiles.
+__device__ __forceinline__ int xcd_tile(int b, int B)
 {
-    const int B = gridDim.x;
-    const int b = blockIdx.x;
-    return (B % 8 == 0) ? (b % 8) * (B / 8) + b / 8 : b;
+    const int x = b & 7, q = B >> 3, r = B & 7;
+    return x * q + min(x, r) + (b >> 3);
 }
+__device__ __forceinline__ int xcd_tile() { return xcd_tile(blockIdx.x, gridDim.x); }
 
 // xcd_tile() with each XCD walking its range from the end: a launch that
 // follows one in the forward order starts on the tiles the other wrote last,
@@ -361,10 +370,14 @@ __device__ __forceinline__ int slab_p(int q, int n, int np) { return q < np ? q 
 void launch_fused(const FusedArgs &a, hipStream_t s);
 void launch_jb_clear(float *Jb, int N, int nx, int ny, int nz, const int *per, const int *pbox, float S,
                      const DevState *st, hipStream_t s);
-void launch_h_update(const FieldArgs &a, hipStream_t s);
+// The H update.  With a.tick and `probe`, its launch also samples E for the step
+// before (extra workgroups, so that the probes cost no launch of their own).
+void launch_h_update(const FieldArgs &a, const ProbeArgs *probe, hipStream_t s);
 void launch_e_update(const FieldArgs &a, hipStream_t s);
 void launch_push_deposit(const PartArgs &a, int mode, hipStream_t s);
-void launch_probe(const ProbeArgs &a, hipStream_t s);  // also advances the DevState
+// The probes of the step just taken, as a launch of its own; advance: it also
+// moves the clock (FieldArgs::tick 0).
+void launch_probe(const ProbeArgs &a, bool advance, hipStream_t s);
 void launch_fill_i32(int *p, int v, long long n, hipStream_t s);
 void launch_sort(const SortArgs &a, int *scan_tmp, hipStream_t s);
 // The sorts of nmem simulations (every one with particles) in one launch per
@@ -377,7 +390,8 @@ int scan_tmp_size(long long n);
 // of per-simulation argument blocks; `own` a device table with one entry per
 // work unit of the launch (field tile / particle workgroup, `total` of them):
 // simulation index << 24 | the unit's index within that simulation.
-void launch_h_update_batch(const FieldArgs *args, const int *own, int total, int shape, hipStream_t s);
+void launch_h_update_batch(const FieldArgs *args, const int *own, int total, int shape, const ProbeArgs *probe,
+                           int nmem, hipStream_t s);
 void launch_e_update_batch(const FieldArgs *args, const int *own, int total, int shape, hipStream_t s);
 void launch_push_deposit_batch(const PartArgs *args, const int *own, int total, int mode, hipStream_t s);
 void launch_probe_batch(const ProbeArgs *args, int n, hipStream_t s);
@@ -442,5 +456,64 @@ struct DiagArgs {
 };
 void launch_rho(const DiagArgs &a, hipStream_t s);
 void launch_diag_reduce(const DiagArgs &a, hipStream_t s);
+
+// ---- probes ----
+
+// sin and cos of x: x less the nearest multiple n of pi/2 (pi/2 as a sum of two
+// doubles, each product exact in the fma), then the Taylor series on [-pi/4,
+// pi/4] (the first terms left out are below 1e-19).  The library function's
+// reduction for huge arguments would take the field kernel that carries the
+// probes to twice its registers.
+__device__ __forceinline__ void sincos_phase(double x, double &sn, double &cs)
+{
+    const double n = rint(x * 0.63661977236758134308);
+    const double r = fma(-n, 6.123233995736766036e-17, fma(-n, 1.5707963267948965580, x));
+    const double z = r * r;
+    double s = -1.0 / 121645100408832000.0, c = -1.0 / 6402373705728000.0;  // -1/19!, -1/18!
+    s = fma(s, z, 1.0 / 355687428096000.0);
+    c = fma(c, z, 1.0 / 20922789888000.0);
+    s = fma(s, z, -1.0 / 1307674368000.0);
+    c = fma(c, z, -1.0 / 87178291200.0);
+    s = fma(s, z, 1.0 / 6227020800.0);
+    c = fma(c, z, 1.0 / 479001600.0);
+    s = fma(s, z, -1.0 / 39916800.0);
+    c = fma(c, z, -1.0 / 3628800.0);
+    s = fma(s, z, 1.0 / 362880.0);
+    c = fma(c, z, 1.0 / 40320.0);
+    s = fma(s, z, -1.0 / 5040.0);
+    c = fma(c, z, -1.0 / 720.0);
+    s = fma(s, z, 1.0 / 120.0);
+    c = fma(c, z, 1.0 / 24.0);
+    s = fma(s, z, -1.0 / 6.0);
+    c = fma(c, z, -0.5);
+    s = fma(r * z, s, r);
+    c = fma(z, c, 1.0);
+    const int q = (int)(n - 4.0 * floor(0.25 * n));
+    const double a = q & 1 ? c : s, b = q & 1 ? s : c;
+    sn = q & 2 ? -a : a;
+    cs = q == 1 || q == 2 ? -b : b;
+}
+
+// F_p(w_m) += dt Ez_p^n exp(-i w_m n dt) for the newest field E^n, n = n1 steps
+// taken (Sec. IV, Figs. 6-7: Ez at the film surface and its spectrum), by one
+// workgroup of nt threads; the phase is evaluated directly in FP64 each step.
+__device__ __forceinline__ void probe_dft(const ProbeArgs &a, long long n1, int t, int nt)
+{
+    const gp<const float> Ez = G(a.Ez);
+    const gp<const int> pidx = G(a.pidx);
+    const double tn = (double)n1 * a.dt;
+    for (int q = t; q < a.nprobe * a.nfreq; q += nt) {
+        const int p = q / a.nfreq, f = q - p * a.nfreq;
+        const double ez = (double)Ez[pidx[p]];
+        double sn, cs;
+        sincos_phase(G(a.omega)[f] * tn, sn, cs);
+        G(a.fre)[q] += a.dt * ez * cs;
+        G(a.fim)[q] -= a.dt * ez * sn;
+    }
+    for (int p = t; p < a.nprobe; p += nt) {
+        if (a.series && n1 - 1 < a.series_len) G(a.series)[(n1 - 1) * a.nprobe + p] = Ez[pidx[p]];
+        if (a.gser && n1 > a.g0 && n1 <= a.g0 + a.gn) G(a.gser)[(n1 - a.g0 - 1) * a.nprobe + p] = (double)Ez[pidx[p]];
+    }
+}
 
 }  // namespace pic
