@@ -16,7 +16,7 @@
 // wavefront mostly share a grid row: the sum over the particles of a row is a
 // small matrix product (x factors times transverse factors) and runs on the
 // matrix cores in FP32 (deposit_rows).  Rows with few lanes use per-lane
-// atomics.  The fixed-point deposit sums integers instead: lanes with equal
+// atomics.  Few particles are spread over more wavefronts (k_push_split).  The fixed-point deposit sums integers instead: lanes with equal
 // windows by recursive halving (64 slots -> one slot per lane), the two widest
 // exchanges by the gfx950 half-wave swaps (v_permlane32_swap,
 // v_permlane16_swap), the four narrow ones by DPP lane moves.
@@ -24,13 +24,14 @@
 
 namespace pic {
 
-// Index on a periodic axis (window indices reach n + 1, which is 2 periods
-// away when n = 1).
+// Index on a periodic axis: a move is shorter than a cell, so window indices
+// reach from -1 to n + 1, which is 2 periods away when n = 1.  (No remainder: an
+// integer division per node took longer than the rest of an edge row's indices.)
 __device__ __forceinline__ int wrapn(int i, int n)
 {
-    if (i >= 0 && i < n) return i;
-    const int r = i % n;
-    return r < 0 ? r + n : r;
+    i += i < 0 ? n : 0;
+    i -= i >= n ? n : 0;
+    return i >= n ? i - n : i;
 }
 
 // Fold a finite coordinate that moved less than one period back into [0, n).
@@ -176,6 +177,17 @@ __device__ __forceinline__ AxisF axis_factors(float x0, float x1, int base)
     f.P[0] = dS[0];
     f.P[1] = dS[0] + dS[1];
     return f;
+}
+
+// The same for one node or edge at grid position n.
+struct SlotF {
+    float A, D, P;
+};
+__device__ __forceinline__ SlotF slot_factors(float x0, float x1, int n)
+{
+    const float e0 = x0 - (float)n, e1 = x1 - (float)n;
+    const float s0 = clamp01(1.f - fabsf(e0)), s1 = clamp01(1.f - fabsf(e1));
+    return {0.5f * (s0 + s1), RSQRT12 * (s1 - s0), clamp01(1.f - e1) - clamp01(1.f - e0)};
 }
 
 // Slot s (0..53) of the deposit window: component and offsets from the base node.
@@ -329,6 +341,35 @@ __device__ __forceinline__ void lane_deposit(const PartArgs &a, const int base[3
     }
 }
 
+// The same with the particle in the 3 lanes of q = 0..2, each for the slots of z
+// node (Jx, Jy) or z edge (Jz) q.
+__device__ __forceinline__ void quarter_deposit(const PartArgs &a, int q, const int base[3], float x0, float y0,
+                                                float z0, float x1, float y1, float z1)
+{
+    const AxisO ox = axis_offsets(base[0], a.nx, a.per[0], 1);
+    const AxisO oy = axis_offsets(base[1], a.ny, a.per[1], a.nx);
+    int k = base[2] + q;
+    const AxisF fx = axis_factors(x0, x1, base[0]), fy = axis_factors(y0, y1, base[1]);
+    const SlotF fz = slot_factors(z0, z1, k);
+    if (a.per[2]) k = wrapn(k, a.nz);
+    if (q > 2 || (unsigned)k >= (unsigned)a.nz) return;
+    const int oz = k * a.nx * a.ny;
+    const float P = q < 2 ? fz.P : 0.f;
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+            if (!(ox.ok[i] && oy.ok[j])) continue;
+            const int o = oz + oy.o[j] + ox.o[i];
+            const float jx = i < 2 ? fx.P[i < 2 ? i : 0] * (fy.A[j] * fz.A + fy.D[j] * fz.D) : 0.f;
+            const float jy = j < 2 ? fy.P[j < 2 ? j : 0] * (fx.A[i] * fz.A + fx.D[i] * fz.D) : 0.f;
+            const float jz = P * (fx.A[i] * fy.A[j] + fx.D[i] * fy.D[j]);
+            if (jx != 0.f) gatomic_add(G(a.Jb[0]) + o, a.qd * jx);
+            if (jy != 0.f) gatomic_add(G(a.Jb[1]) + o, a.qd * jy);
+            if (jz != 0.f) gatomic_add(G(a.Jb[2]) + o, a.qd * jz);
+        }
+}
+
 // ---- deposit of the lanes of one grid row (matrix cores) ----
 // The lanes of a pass share their windows' y and z base (by, bz) and have x
 // bases in [X0, X0 + 13], so their windows lie on 16 x nodes X0 + t.  Every
@@ -349,11 +390,10 @@ __device__ __forceinline__ void lane_deposit(const PartArgs &a, const int base[3
 // wavefronts' VALU) whatever the number and order of the windows, where summing
 // every slot over the lanes takes 324 for one ordered row and 220 per window
 // otherwise.  512x256x256 cells, 1e7 particles: 351 -> 276 us per launch; 1e6
-// particles in a 64x128x128 box periodic along x: 94 -> 63 us; 4000 particles
-// (63 wavefronts, one cell across y): 22.5 -> 14.8 us.
+// particles in a 64x128x128 box periodic along x: 94 -> 63 us.
 constexpr int ROW_NODES = 16;
 constexpr int ROW_BASES = ROW_NODES - 2;
-// Rows with fewer lanes go to the per-lane atomics, whose cost does not depend
+// Rows with fewer lanes go to the per-lane atomics (lane_deposit), whose cost does not depend
 // on how many rows they come from: a pass costs a wavefront a chain of LDS reads
 // and matrix products and eight atomics, and the wavefronts of a bunch's tails
 // hold many short rows.  Push of 1e5 particles in a 128x64x64 box, the slowest
@@ -363,6 +403,7 @@ constexpr int ROW_BASES = ROW_NODES - 2;
 constexpr int ROW_LANES = 10;
 
 typedef float fvec4 __attribute__((ext_vector_type(4)));
+constexpr float ROW_FAR = 1e9f;
 
 struct RowLds {
     float4 pair[64][3];  // per particle (A, D) at y nodes 0..2, then z nodes 0..2
@@ -370,24 +411,21 @@ struct RowLds {
     float2 x[64];        // x0, x1
 };
 
-__device__ __forceinline__ void row_factors(RowLds &L, int lane, const AxisF &fy, const AxisF &fz)
+__device__ __forceinline__ void row_factors(RowLds &L, int p, const AxisF &fy, const AxisF &fz)
 {
-    L.pair[lane][0] = make_float4(fy.A[0], fy.D[0], fy.A[1], fy.D[1]);
-    L.pair[lane][1] = make_float4(fy.A[2], fy.D[2], fz.A[0], fz.D[0]);
-    L.pair[lane][2] = make_float4(fz.A[1], fz.D[1], fz.A[2], fz.D[2]);
-    L.pre[lane] = make_float4(fy.P[0], fy.P[1], fz.P[0], fz.P[1]);
+    L.pair[p][0] = make_float4(fy.A[0], fy.D[0], fy.A[1], fy.D[1]);
+    L.pair[p][1] = make_float4(fy.A[2], fy.D[2], fz.A[0], fz.D[0]);
+    L.pair[p][2] = make_float4(fz.A[1], fz.D[1], fz.A[2], fz.D[2]);
+    L.pre[p] = make_float4(fy.P[0], fy.P[1], fz.P[0], fz.P[1]);
 }
 
-// m: the pass's lanes; yz: some lane of the wavefront moves along y or z.
-__device__ __forceinline__ void deposit_rows(const PartArgs &a, RowLds &L, unsigned long long m, bool mine, int lane,
-                                             float x0, float x1, int X0, int by, int bz, bool yz)
+// Adds the 16 particles from p0 on to the sums of a pass whose first x node is
+// X0.  MASK: only those whose bit of m16 is set (otherwise L.x has the rest far
+// away).
+template <bool MASK>
+__device__ __forceinline__ void row_chunk(const RowLds &L, int p0, unsigned m16, int lane, int X0, bool yz, fvec4 &jx,
+                                          fvec4 &jyz)
 {
-    const float far = 1e9f;
-    // one wavefront per workgroup: its LDS operations execute in program
-    // order, the wave barriers keep the compiler from moving them
-    __builtin_amdgcn_wave_barrier();
-    L.x[lane] = mine ? make_float2(x0, x1) : make_float2(far, far);
-    __builtin_amdgcn_wave_barrier();
     const int t = lane & 15, q = lane >> 4;
     // Row t of Jx is (b, c) = (t/2, t%3) for t < 6 and (t - 6, 8 - t) for t =
     // 6..8; row t of Jy, Jz is edge m = t/3, z node c = t%3 of Jy for t < 6,
@@ -399,74 +437,110 @@ __device__ __forceinline__ void deposit_rows(const PartArgs &a, RowLds &L, unsig
     const float2 *pairs = reinterpret_cast<const float2 *>(L.pair) + q * 6;
     const float *pres = reinterpret_cast<const float *>(L.pre) + q * 4 + np;
     const float ct = (float)(X0 + t);
-    fvec4 jx = {0.f, 0.f, 0.f, 0.f}, jyz = {0.f, 0.f, 0.f, 0.f};
-    for (int d = 0; d < 4; ++d) {
-        if (!((m >> (16 * d)) & 0xffffull)) continue;
-        float2 v1[4], v2[4], xx[4];
-        float pr[4];
+    const unsigned mq = m16 >> q;
+    float2 v1[4], v2[4], xx[4];
+    float pr[4];
 #pragma unroll
-        for (int g = 0; g < 4; ++g) {
-            const int p = 16 * d + 4 * g;
-            v1[g] = pairs[p * 6 + n1];
-            v2[g] = pairs[p * 6 + n2];
-            xx[g] = L.x[p + q];
-            pr[g] = pres[p * 4];
-        }
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-            const float e0 = xx[g].x - ct, e1 = xx[g].y - ct;
-            // running sums of the shapes up to node t, after less before
-            const float px = clamp01(1.f - e1) - clamp01(1.f - e0);
-            const float T = v1[g].x * v2[g].x + v1[g].y * v2[g].y;
-            jx = __builtin_amdgcn_mfma_f32_16x16x4f32(T, px, jx, 0, 0, 0);
-            if (yz) {
-                const float s0 = clamp01(1.f - fabsf(e0)), s1 = clamp01(1.f - fabsf(e1));
-                // 2 A and 2 D along x: the factor 1/2 is applied to the sums
-                jyz = __builtin_amdgcn_mfma_f32_16x16x4f32(pr[g] * v1[g].x, s0 + s1, jyz, 0, 0, 0);
-                jyz = __builtin_amdgcn_mfma_f32_16x16x4f32(pr[g] * v1[g].y, (2.f * RSQRT12) * (s1 - s0), jyz, 0, 0, 0);
-            }
-        }
+    for (int g = 0; g < 4; ++g) {
+        const int p = p0 + 4 * g;
+        v1[g] = pairs[p * 6 + n1];
+        v2[g] = pairs[p * 6 + n2];
+        xx[g] = L.x[p + q];
+        pr[g] = pres[p * 4];
     }
-    // lane l holds column t of rows 4 q + j, j = 0..3: the rows' transverse
-    // offsets (oj | ok << 2) packed four to a word, by q
-    const int wx = q == 0 ? 0x1940 : (q == 1 ? 0x58a6 : 0x0002);
-    const int wyz = q == 0 ? 0x1840 : (q == 1 ? 0x1095 : 0x6542);
-    const int nxr = q < 2 ? 4 : (q == 2 ? 1 : 0), nyzr = q < 3 ? 4 : 0;
-    const int sy = a.nx, sz = a.nx * a.ny;
-    const bool inside = X0 >= 0 && X0 + ROW_NODES <= a.nx && by >= 0 && by + 2 < a.ny && bz >= 0 && bz + 2 < a.nz;
-    const float qd = a.qd;
-    if (inside) {
-        const int cell = X0 + a.nx * (by + a.ny * bz) + t;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int o = cell + sy * ((wx >> (4 * j)) & 3) + sz * ((wx >> (4 * j + 2)) & 3);
-            if (j < nxr && jx[j] != 0.f) gatomic_add(G(a.Jb[0]) + o, qd * jx[j]);
-        }
+    for (int g = 0; g < 4; ++g) {
+        const bool in = !MASK || ((mq >> (4 * g)) & 1u);
+        const float e0 = in ? xx[g].x - ct : ROW_FAR, e1 = in ? xx[g].y - ct : ROW_FAR;
+        // running sums of the shapes up to node t, after less before
+        const float px = clamp01(1.f - e1) - clamp01(1.f - e0);
+        const float T = v1[g].x * v2[g].x + v1[g].y * v2[g].y;
+        jx = __builtin_amdgcn_mfma_f32_16x16x4f32(T, px, jx, 0, 0, 0);
         if (yz) {
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int o = cell + sy * ((wyz >> (4 * j)) & 3) + sz * ((wyz >> (4 * j + 2)) & 3);
-                float *J = 4 * q + j < 6 ? a.Jb[1] : a.Jb[2];
-                if (j < nyzr && jyz[j] != 0.f) gatomic_add(G(J) + o, (0.5f * qd) * jyz[j]);
-            }
-        }
-    } else {
-        const int i = a.per[0] ? wrapn(X0 + t, a.nx) : X0 + t;
-        const bool okx = i >= 0 && i < a.nx;
-        const AxisO oy = axis_offsets(by, a.ny, a.per[1], sy), oz = axis_offsets(bz, a.nz, a.per[2], sz);
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const int w = ((j < 4 ? wx : wyz) >> (4 * (j & 3))) & 15;
-            const int oj = w & 3, ok = w >> 2;
-            const int o = i + (oj == 0 ? oy.o[0] : (oj == 1 ? oy.o[1] : oy.o[2])) +
-                          (ok == 0 ? oz.o[0] : (ok == 1 ? oz.o[1] : oz.o[2]));
-            const bool in = okx && (oj == 0 ? oy.ok[0] : (oj == 1 ? oy.ok[1] : oy.ok[2])) &&
-                            (ok == 0 ? oz.ok[0] : (ok == 1 ? oz.ok[1] : oz.ok[2]));
-            const float v = j < 4 ? jx[j & 3] : jyz[j & 3];
-            float *J = j < 4 ? a.Jb[0] : (4 * q + (j & 3) < 6 ? a.Jb[1] : a.Jb[2]);
-            if (in && (j & 3) < (j < 4 ? nxr : nyzr) && v != 0.f) gatomic_add(G(J) + o, (j < 4 ? qd : 0.5f * qd) * v);
+            const float s0 = clamp01(1.f - fabsf(e0)), s1 = clamp01(1.f - fabsf(e1));
+            // 2 A and 2 D along x: the factor 1/2 is applied to the sums
+            jyz = __builtin_amdgcn_mfma_f32_16x16x4f32(pr[g] * v1[g].x, s0 + s1, jyz, 0, 0, 0);
+            jyz = __builtin_amdgcn_mfma_f32_16x16x4f32(pr[g] * v1[g].y, (2.f * RSQRT12) * (s1 - s0), jyz, 0, 0, 0);
         }
     }
+}
+
+// Where a pass's sums go.  Lane l holds column t of rows 4 q + j, j = 0..3, of Jx
+// and of (Jy, Jz: rows 0..5 and 6..11).  The rows' transverse offsets oj + 3 ok
+// are packed four bits each, by q; lane oj + 3 ok works out where that grid row
+// starts (-1 outside the grid), and the others fetch it from there.
+struct RowOut {
+    int i, start, wx, wyz;  // i: the column's x index, or -1
+};
+
+__device__ __forceinline__ RowOut row_out(const PartArgs &a, int lane, int X0, int by, int bz)
+{
+    const int t = lane & 15, q = lane >> 4;
+    int i = X0 + t, j = by + t % 3, k = bz + t / 3;
+    if (a.per[0]) i = wrapn(i, a.nx);
+    if (a.per[1]) j = wrapn(j, a.ny);
+    if (a.per[2]) k = wrapn(k, a.nz);
+    const bool ok = (unsigned)j < (unsigned)a.ny && (unsigned)k < (unsigned)a.nz;
+    RowOut r;
+    r.i = (unsigned)i < (unsigned)a.nx ? i : -1;
+    r.start = ok ? a.nx * (j + a.ny * k) : -1;
+    r.wx = q == 0 ? 0x1730 : (q == 1 ? 0x4685 : 0x2);
+    r.wyz = q == 0 ? 0x1630 : (q == 1 ? 0x1074 : 0x5432);
+    return r;
+}
+
+__device__ __forceinline__ void row_add(const PartArgs &a, const RowOut &r, int lane, int j, bool yz, float jx,
+                                        float jyz)
+{
+    const int q = lane >> 4;
+    const int ox = __builtin_amdgcn_ds_bpermute(((r.wx >> (4 * j)) & 15) << 2, r.start);
+    if (min(r.i, ox) >= 0 && 4 * q + j < 9 && jx != 0.f) gatomic_add(G(a.Jb[0]) + (ox + r.i), a.qd * jx);
+    if (!yz) return;
+    const int oyz = __builtin_amdgcn_ds_bpermute(((r.wyz >> (4 * j)) & 15) << 2, r.start);
+    float *J = 4 * q + j < 6 ? a.Jb[1] : a.Jb[2];
+    if (min(r.i, oyz) >= 0 && q < 3 && jyz != 0.f) gatomic_add(G(J) + (oyz + r.i), (0.5f * a.qd) * jyz);
+}
+
+// m: the pass's lanes; yz: some lane of the wavefront moves along y or z.
+__device__ __forceinline__ void deposit_rows(const PartArgs &a, RowLds &L, unsigned long long m, int lane, float x0,
+                                             float x1, int X0, int by, int bz, bool yz)
+{
+    const bool mine = (m >> lane) & 1ull;
+    // one wavefront per workgroup: its LDS operations execute in program
+    // order, the wave barriers keep the compiler from moving them
+    __builtin_amdgcn_wave_barrier();
+    L.x[lane] = mine ? make_float2(x0, x1) : make_float2(ROW_FAR, ROW_FAR);
+    __builtin_amdgcn_wave_barrier();
+    fvec4 jx = {0.f, 0.f, 0.f, 0.f}, jyz = {0.f, 0.f, 0.f, 0.f};
+    for (int d = 0; d < 4; ++d)
+        if ((m >> (16 * d)) & 0xffffull) row_chunk<false>(L, 16 * d, 0, lane, X0, yz, jx, jyz);
+    const RowOut r = row_out(a, lane, X0, by, bz);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) row_add(a, r, lane, j, yz, jx[j], jyz[j]);
+}
+
+// relativistic Boris: half kick, rotation, half kick (u in units of c)
+__device__ __forceinline__ void boris(float ah, float e0, float e1, float e2, float h0, float h1, float h2, float &u0,
+                                      float &u1, float &u2)
+{
+    const float m0 = u0 + ah * e0, m1 = u1 + ah * e1, m2 = u2 + ah * e2;
+    const float gi = rsqrtf(1.f + m0 * m0 + m1 * m1 + m2 * m2);
+    const float t0 = ah * h0 * gi, t1 = ah * h1 * gi, t2 = ah * h2 * gi;
+    const float f = 2.f / (1.f + t0 * t0 + t1 * t1 + t2 * t2);
+    const float s0 = f * t0, s1 = f * t1, s2 = f * t2;
+    const float p0 = m0 + (m1 * t2 - m2 * t1);
+    const float p1 = m1 + (m2 * t0 - m0 * t2);
+    const float p2 = m2 + (m0 * t1 - m1 * t0);
+    u0 = m0 + (p1 * s2 - p2 * s1) + ah * e0;
+    u1 = m1 + (p2 * s0 - p0 * s2) + ah * e1;
+    u2 = m2 + (p0 * s1 - p1 * s0) + ah * e2;
+}
+
+// A move that leaves through a wall, or is not finite, deactivates the particle.
+__device__ __forceinline__ bool leaves(const PartArgs &a, float x, float y, float z)
+{
+    return !(isfinite(x) && isfinite(y) && isfinite(z)) || (!a.per[0] && !(x >= 0.f && x < (float)a.nx)) ||
+           (!a.per[1] && !(y >= 0.f && y < (float)a.ny)) || (!a.per[2] && !(z >= 0.f && z < (float)a.nz));
 }
 
 // Fixed-point deposit: a window shared by at least ROUND_LANES lanes is summed
@@ -474,6 +548,26 @@ __device__ __forceinline__ void deposit_rows(const PartArgs &a, RowLds &L, unsig
 // the lanes of smaller windows add their slots with per-lane atomics, all such
 // lanes of the wavefront together (54 atomic instructions however many lanes).
 constexpr int ROUND_LANES = 3;
+
+// The passes of a wavefront's rows with at least ROW_LANES lanes; the lanes left over.
+__device__ __forceinline__ unsigned long long row_passes(const PartArgs &a, RowLds &L, unsigned long long rem,
+                                                         int lane, const int base[3], float x0, float x1, bool yz)
+{
+    unsigned long long small = 0;
+    while (rem) {
+        const int leader = __ffsll((long long)rem) - 1;
+        // a lane behind the leader by less than a cell still joins its pass
+        const int X0 = __builtin_amdgcn_readlane(base[0], leader) - 1;
+        const int by = __builtin_amdgcn_readlane(base[1], leader);
+        const int bz = __builtin_amdgcn_readlane(base[2], leader);
+        const unsigned long long m =
+            __ballot(base[1] == by && base[2] == bz && (unsigned)(base[0] - X0) < (unsigned)ROW_BASES) & rem;
+        rem &= ~m;
+        if (__popcll(m) < ROW_LANES) small |= m;
+        else deposit_rows(a, L, m, lane, x0, x1, X0, by, bz, yz);
+    }
+    return small;
+}
 
 template <int MODE, int PX, int FIX>
 __device__ __forceinline__ void push_body(const PartArgs &a, int blk)
@@ -531,28 +625,12 @@ __device__ __forceinline__ void push_body(const PartArgs &a, int blk)
                 h1 = gather_pair<1, 0, 1>(a.B[1], XP, AY, AZ);
                 h2 = gather_pair<1, 1, 0>(a.B[2], XP, AY, AZ);
             }
-            // relativistic Boris: half kick, rotation, half kick (u in units of c)
-            const float ah = a.ah;
-            const float m0 = u0 + ah * e0, m1 = u1 + ah * e1, m2 = u2 + ah * e2;
-            const float gi = rsqrtf(1.f + m0 * m0 + m1 * m1 + m2 * m2);
-            const float t0 = ah * h0 * gi, t1 = ah * h1 * gi, t2 = ah * h2 * gi;
-            const float f = 2.f / (1.f + t0 * t0 + t1 * t1 + t2 * t2);
-            const float s0 = f * t0, s1 = f * t1, s2 = f * t2;
-            const float p0 = m0 + (m1 * t2 - m2 * t1);
-            const float p1 = m1 + (m2 * t0 - m0 * t2);
-            const float p2 = m2 + (m0 * t1 - m1 * t0);
-            u0 = m0 + (p1 * s2 - p2 * s1) + ah * e0;
-            u1 = m1 + (p2 * s0 - p0 * s2) + ah * e1;
-            u2 = m2 + (p0 * s1 - p1 * s0) + ah * e2;
+            boris(a.ah, e0, e1, e2, h0, h1, h2, u0, u1, u2);
         }
         if (live) {
             const float g = rsqrtf(1.f + u0 * u0 + u1 * u1 + u2 * u2);
             const float nx1 = x + a.S * u0 * g, ny1 = y + a.S * u1 * g, nz1 = z + a.S * u2 * g;
-            // leaving through a wall, or a non-finite move, deactivates the particle
-            const bool out = !(isfinite(nx1) && isfinite(ny1) && isfinite(nz1)) ||
-                             (!a.per[0] && !(nx1 >= 0.f && nx1 < (float)a.nx)) ||
-                             (!a.per[1] && !(ny1 >= 0.f && ny1 < (float)a.ny)) ||
-                             (!a.per[2] && !(nz1 >= 0.f && nz1 < (float)a.nz));
+            const bool out = leaves(a, nx1, ny1, nz1);
             __builtin_nontemporal_store(u0, UX + p);
             __builtin_nontemporal_store(u1, UY + p);
             __builtin_nontemporal_store(u2, UZ + p);
@@ -631,21 +709,7 @@ __device__ __forceinline__ void push_body(const PartArgs &a, int blk)
         const AxisF fy = axis_factors(y0, y1, base[1]), fz = axis_factors(z0, z1, base[2]);
         row_factors(L, lane, fy, fz);
         const bool yz = __ballot(fy.P[0] != 0.f || fy.P[1] != 0.f || fz.P[0] != 0.f || fz.P[1] != 0.f) != 0ull;
-        unsigned long long small = 0;
-        while (rem) {
-            const int leader = __ffsll((long long)rem) - 1;
-            // a lane behind the leader by less than a cell still joins its pass
-            const int X0 = __builtin_amdgcn_readlane(base[0], leader) - 1;
-            const int by = __builtin_amdgcn_readlane(base[1], leader);
-            const int bz = __builtin_amdgcn_readlane(base[2], leader);
-            const bool mine = ((rem >> lane) & 1ull) && base[1] == by && base[2] == bz &&
-                              (unsigned)(base[0] - X0) < (unsigned)ROW_BASES;
-            const unsigned long long m = __ballot(mine);
-            rem &= ~m;
-            if (__popcll(m) < ROW_LANES) small |= m;
-            else deposit_rows(a, L, m, mine, lane, x0, x1, X0, by, bz, yz);
-        }
-        rem = small;
+        rem = row_passes(a, L, rem, lane, base, x0, x1, yz);
     }
     if ((rem >> lane) & 1ull) {
         const AxisF fx = axis_factors(x0, x1, base[0]), fy = axis_factors(y0, y1, base[1]),
@@ -664,6 +728,200 @@ __device__ __forceinline__ void push_body(const PartArgs &a, int blk)
 // and started last they would run on alone (1e6 particles in a 448x128x128 box
 // 54.0 -> 48.3 us, in 64x128x128 62.2 -> 55.4 us).
 __device__ __forceinline__ int ends_first(int b, int n) { return b & 1 ? n - 1 - (b >> 1) : b >> 1; }
+
+// ---- few particles: 16 a wavefront, 4 lanes each ----
+// With few particles the push takes as long as its slowest wavefront, and a
+// wavefront that has a SIMD to itself takes as long as the instructions it
+// issues one after another: of 26000 cycles, 2000 for the gather, 4500 for each
+// row's pass, 5500 for the lanes of short rows.  So a wavefront gets 16
+// particles: 4 lanes share a particle, each gathers one (y, z) corner and adds
+// one third of a short row's slots; a pass takes 16 particles.  The four
+// wavefronts of a workgroup hold the 64 particles of a plain one's and go through
+// the same passes.  One that 3 or 4 of them have particles in is summed in LDS,
+// and each adds a quarter of the slots: atomics on one cache line follow each
+// other at 12.7 ns, and without this a dense bunch (2e4 particles on 150 lines)
+// took 23 us, otherwise 8.  Long loops over wide rows in dense bunches are what
+// the plain kernel is for.
+//
+// Plain kernel / this one, us: 1000 particles 10.8 / 7.8, 4000 in a sheet 12.9 /
+// 8.4, 2e4 in a 91x45x53 box 13.0 / 8.6, 3e4 in 448x128x128 10.6 / 8.7, 5e4 in
+// 128x64x64 13.5 / 10.6, 6e4 in 448x128x128 11.9 / 10.2, 6e4 periodic along x
+// 14.3 / 14.3, 1e5 14.3 / 14.1 and 12.0 / 13.8, 2e5 15.2 / 19.6.
+constexpr int SPLIT_MAX = 1 << 16;
+// Rows with fewer particles of the workgroup go to quarter_deposit, whose time does
+// not depend on their number (2e4 particles, least number 4, 7, 10, 16: 13.4,
+// 11.3, 9.8, 8.6 us; 1000: 9.5, 9.0, 8.4, 7.8).
+constexpr int SPLIT_LANES = 16;
+
+// The sum over the 4 lanes l, l ^ 16, l ^ 32, l ^ 48, the same in each of them.
+__device__ __forceinline__ float quad_sum(float v)
+{
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+    const auto t = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return __uint_as_float(t[0]) + __uint_as_float(t[1]);
+}
+
+// One (y, z) corner of the gather, by node and half node: offset and weight.
+struct Corner {
+    int o[2];
+    float m[2];
+};
+
+__device__ __forceinline__ Corner corner(const Axis2 &A, int c)
+{
+    Corner r;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        r.o[h] = c ? A.o1[h] : A.o0[h];
+        r.m[h] = c ? A.m1[h] : A.m0[h];
+    }
+    return r;
+}
+
+template <int HX, int HY, int HZ>
+__device__ __forceinline__ float corner_pair(const float *__restrict__ f, const XPair &X, const Corner &Y,
+                                             const Corner &Z)
+{
+    const float2 p = ld2(f + (X.o[HX] + Y.o[HY] + Z.o[HZ]));
+    return Y.m[HY] * Z.m[HZ] * (X.wa[HX] * p.x + X.wb[HX] * p.y);
+}
+
+template <int HX, int HY, int HZ>
+__device__ __forceinline__ float corner_scalar(const float *__restrict__ f, const Axis2 &X, const Corner &Y,
+                                               const Corner &Z)
+{
+    const int o = Y.o[HY] + Z.o[HZ];
+    const float p = G(f)[X.o0[HX] + o], q = G(f)[X.o1[HX] + o];
+    return Y.m[HY] * Z.m[HZ] * (X.m0[HX] * p + X.m1[HX] * q);
+}
+
+template <int PX>
+__global__ __launch_bounds__(256) void k_push_split(PartArgs a)
+{
+    const int lane = threadIdx.x & 63, c = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int slot = 16 * wave + (lane & 15);
+    const int blk = ends_first(blockIdx.x, gridDim.x), p = blk * PUSH_BLOCK + slot;
+    const gp<const DevState> st = G(a.st);
+    const gp<float> __restrict__ X = G(st->P[0]);
+    const gp<float> __restrict__ Y = G(st->P[1]);
+    const gp<float> __restrict__ Z = G(st->P[2]);
+    const gp<float> __restrict__ UX = G(st->P[3]);
+    const gp<float> __restrict__ UY = G(st->P[4]);
+    const gp<float> __restrict__ UZ = G(st->P[5]);
+    const int q = min(p, a.n - 1);
+    const float x = X[q], y = Y[q], z = Z[q];
+    float u0 = UX[q], u1 = UY[q], u2 = UZ[q];
+    const bool had = p < a.n && live_pos(x, y, z, a.nx, a.ny, a.nz);
+    const float xg = had ? x : 0.f, yg = had ? y : 0.f, zg = had ? z : 0.f;
+    {
+        Axis2 AY, AZ;
+        axis_corners(yg, a.ny, a.per[1], a.nx, AY);
+        axis_corners(zg, a.nz, a.per[2], a.nx * a.ny, AZ);
+        const Corner CY = corner(AY, c & 1), CZ = corner(AZ, c >> 1);
+        float e0, e1, e2, h0, h1, h2;
+        if (PX) {
+            Axis2 AX;
+            axis_corners(xg, a.nx, a.per[0], 1, AX);
+            e0 = corner_scalar<1, 0, 0>(a.E[0], AX, CY, CZ);
+            e1 = corner_scalar<0, 1, 0>(a.E[1], AX, CY, CZ);
+            e2 = corner_scalar<0, 0, 1>(a.E[2], AX, CY, CZ);
+            h0 = corner_scalar<0, 1, 1>(a.B[0], AX, CY, CZ);
+            h1 = corner_scalar<1, 0, 1>(a.B[1], AX, CY, CZ);
+            h2 = corner_scalar<1, 1, 0>(a.B[2], AX, CY, CZ);
+        } else {
+            XPair XP;
+            x_pairs(xg, a.nx, XP);
+            e0 = corner_pair<1, 0, 0>(a.E[0], XP, CY, CZ);
+            e1 = corner_pair<0, 1, 0>(a.E[1], XP, CY, CZ);
+            e2 = corner_pair<0, 0, 1>(a.E[2], XP, CY, CZ);
+            h0 = corner_pair<0, 1, 1>(a.B[0], XP, CY, CZ);
+            h1 = corner_pair<1, 0, 1>(a.B[1], XP, CY, CZ);
+            h2 = corner_pair<1, 1, 0>(a.B[2], XP, CY, CZ);
+        }
+        boris(a.ah, quad_sum(e0), quad_sum(e1), quad_sum(e2), quad_sum(h0), quad_sum(h1), quad_sum(h2), u0, u1, u2);
+    }
+    const float g = rsqrtf(1.f + u0 * u0 + u1 * u1 + u2 * u2);
+    const float nx1 = x + a.S * u0 * g, ny1 = y + a.S * u1 * g, nz1 = z + a.S * u2 * g;
+    const bool dep = had && !leaves(a, nx1, ny1, nz1);
+    if (had && c == 0) {
+        UX[p] = u0;
+        UY[p] = u1;
+        UZ[p] = u2;
+        X[p] = dep ? (a.per[0] ? fold(nx1, a.nx) : nx1) : -1.f;
+        if (dep) {
+            Y[p] = a.per[1] ? fold(ny1, a.ny) : ny1;
+            Z[p] = a.per[2] ? fold(nz1, a.nz) : nz1;
+        }
+    }
+    const float x0 = dep ? x : 0.f, y0 = dep ? y : 0.f, z0 = dep ? z : 0.f;
+    const float x1 = dep ? nx1 : 0.f, y1 = dep ? ny1 : 0.f, z1 = dep ? nz1 : 0.f;
+    const int base[3] = {min((int)floorf(x0), (int)floorf(x1)), min((int)floorf(y0), (int)floorf(y1)),
+                         min((int)floorf(z0), (int)floorf(z1))};
+    __shared__ RowLds L;
+    __shared__ int4 B[PUSH_BLOCK];
+    __shared__ float R[2][4][8][64];
+    {
+        const AxisF fy = axis_factors(y0, y1, base[1]), fz = axis_factors(z0, z1, base[2]);
+        const bool yz = fy.P[0] != 0.f || fy.P[1] != 0.f || fz.P[0] != 0.f || fz.P[1] != 0.f;
+        if (c == 0) {
+            row_factors(L, slot, fy, fz);
+            L.x[slot] = make_float2(x0, x1);
+            B[slot] = make_int4(base[0], base[1], base[2], dep ? (yz ? 3 : 1) : 0);
+        }
+    }
+    __syncthreads();
+    const int4 b = B[lane];
+    unsigned long long rem = __ballot(b.w & 1), small = 0;
+    const bool yz = __ballot(b.w & 2) != 0ull;
+    if (threadIdx.x == 0 && rem) gatomic_add(G(a.pushes) + blk, (unsigned long long)__popcll(rem));
+    int buf = 0;
+    while (rem) {
+        const int leader = __ffsll((long long)rem) - 1;
+        const int X0 = __builtin_amdgcn_readlane(b.x, leader) - 1;
+        const int by = __builtin_amdgcn_readlane(b.y, leader);
+        const int bz = __builtin_amdgcn_readlane(b.z, leader);
+        const unsigned long long m = __ballot(b.y == by && b.z == bz && (unsigned)(b.x - X0) < (unsigned)ROW_BASES) & rem;
+        rem &= ~m;
+        if (__popcll(m) < SPLIT_LANES) {
+            small |= m;
+            continue;
+        }
+        const unsigned own = (unsigned)(m >> (16 * wave)) & 0xffffu;
+        fvec4 jx = {0.f, 0.f, 0.f, 0.f}, jyz = {0.f, 0.f, 0.f, 0.f};
+        if (own) row_chunk<true>(L, 16 * wave, own, lane, X0, yz, jx, jyz);
+        int waves = 0;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) waves += ((m >> (16 * w)) & 0xffffull) != 0;
+        if (waves < 3) {
+            if (own) {
+                const RowOut r = row_out(a, lane, X0, by, bz);
+#pragma unroll
+                for (int j = 0; j < 4; ++j) row_add(a, r, lane, j, yz, jx[j], jyz[j]);
+            }
+            continue;
+        }
+        if (own) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                R[buf][wave][j][lane] = jx[j];
+                R[buf][wave][4 + j][lane] = jyz[j];
+            }
+        }
+        __syncthreads();
+        float sx = 0.f, syz = 0.f;
+#pragma unroll
+        for (int w = 0; w < 4; ++w)
+            if ((m >> (16 * w)) & 0xffffull) {
+                sx += R[buf][w][wave][lane];
+                syz += R[buf][w][4 + wave][lane];
+            }
+        row_add(a, row_out(a, lane, X0, by, bz), lane, wave, yz, sx, syz);
+        buf ^= 1;
+    }
+    if ((small >> slot) & 1ull) quarter_deposit(a, c, base, x0, y0, z0, x1, y1, z1);
+}
 
 template <int MODE, int PX, int FIX>
 __global__ __launch_bounds__(PUSH_BLOCK) void k_push_deposit(PartArgs a)
@@ -687,6 +945,11 @@ void launch_push_deposit(const PartArgs &a, int mode, hipStream_t s)
     const int nb = (int)(((long long)a.n + PUSH_BLOCK - 1) / PUSH_BLOCK);
     // mode 2: wavefront-reduced deposit into the fixed-point current
     const bool fix = mode == 2 && a.Jq[0];
+    if (mode == 0 && a.n <= SPLIT_MAX) {
+        if (a.per[0]) hipLaunchKernelGGL((k_push_split<1>), dim3(nb), dim3(256), 0, s, a);
+        else hipLaunchKernelGGL((k_push_split<0>), dim3(nb), dim3(256), 0, s, a);
+        return;
+    }
     if (a.per[0]) {
         if (fix) hipLaunchKernelGGL((k_push_deposit<0, 1, 1>), dim3(nb), dim3(PUSH_BLOCK), 0, s, a);
         else if (mode == 1) hipLaunchKernelGGL((k_push_deposit<1, 1, 0>), dim3(nb), dim3(PUSH_BLOCK), 0, s, a);
