@@ -92,7 +92,7 @@ __device__ __forceinline__ void atomic_max_pos(double *addr, double v)
 
 // acc layout: [0] sum (E^2 + Ht^2), [1] count, [2..4] sum x, [5..7] sum x^2,
 // [8..10] sum u, [11] max |G|, [12] max |rho0|, [13] checked nodes
-__global__ void k_diag_fields(DiagArgs a)
+__global__ __launch_bounds__(256) void k_diag_fields(DiagArgs a)
 {
     const long long n = (long long)a.nx * a.ny * a.nz;
     double s = 0.0;
@@ -103,8 +103,13 @@ __global__ void k_diag_fields(DiagArgs a)
             s += e * e + h * h;
         }
     }
+    // (one atomic per workgroup: they follow each other at 13 ns, and one per
+    // wavefront took 52 us on the smallest grid)
+    __shared__ double part[4];
     s = warp_sum(s);
-    if ((threadIdx.x & 63) == 0) atomicAdd(&a.acc[0], s);
+    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = s;
+    __syncthreads();
+    if (threadIdx.x == 0) atomicAdd(&a.acc[0], part[0] + part[1] + part[2] + part[3]);
 }
 
 // Grid-stride sums over the live particles, reduced per wavefront, then per
@@ -177,6 +182,45 @@ __global__ void k_diag_gauss(DiagArgs a)
         atomic_max_pos(&a.acc[12], rm);
         atomicAdd(&a.acc[13], cnt);
     }
+}
+
+// Live particles and pushes, summed per workgroup into out[2 b], out[2 b + 1] (the
+// host adds the pairs up: no word to clear first, no atomics on one address), and
+// the particle box behind them.
+__global__ __launch_bounds__(STATS_BLOCK) void k_stats(DiagArgs a, const unsigned long long *pushes, int nslots,
+                                                       const int *box, unsigned long long *out)
+{
+    const int t = blockIdx.x * STATS_BLOCK + threadIdx.x, step = gridDim.x * STATS_BLOCK;
+    int live = 0;
+#pragma unroll 4
+    for (long long p = t; p < a.np; p += step) live += live_pos(a.x[p], a.y[p], a.z[p], a.nx, a.ny, a.nz);
+    unsigned long long n = 0;
+    for (long long w = t; w < nslots; w += step) n += pushes[w];
+    __shared__ unsigned long long part[STATS_BLOCK / 64][2];
+    unsigned long long l = live;
+    for (int off = 32; off > 0; off >>= 1) {
+        l += __shfl_xor(l, off, 64);
+        n += __shfl_xor(n, off, 64);
+    }
+    if ((threadIdx.x & 63) == 0) {
+        part[threadIdx.x >> 6][0] = l;
+        part[threadIdx.x >> 6][1] = n;
+    }
+    __syncthreads();
+    if (threadIdx.x < 2) {
+        unsigned long long v = 0;
+        for (int w = 0; w < STATS_BLOCK / 64; ++w) v += part[w][threadIdx.x];
+        out[2 * blockIdx.x + threadIdx.x] = v;
+    }
+    if (blockIdx.x == 0 && threadIdx.x < 6) reinterpret_cast<int *>(out + 2 * STATS_BLOCKS)[threadIdx.x] = box[threadIdx.x];
+}
+
+int launch_stats(const DiagArgs &a, const unsigned long long *pushes, int nslots, const int *box,
+                 unsigned long long *out, hipStream_t s)
+{
+    const int nb = (int)std::min<long long>(STATS_BLOCKS, ((long long)a.np + STATS_BLOCK - 1) / STATS_BLOCK);
+    hipLaunchKernelGGL(k_stats, dim3(nb), dim3(STATS_BLOCK), 0, s, a, pushes, nslots, box, out);
+    return nb;
 }
 
 void launch_diag_reduce(const DiagArgs &a, hipStream_t s)

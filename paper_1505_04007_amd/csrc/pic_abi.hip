@@ -619,7 +619,7 @@ static pic_status init_impl(pic_ctx *c, const pic_grid *grid, double dx, double 
     }
     TRY(dalloc(c, &c->d_nan, 1));
     HIP_TRY(c, hipMemsetAsync(c->d_nan, 0, 4, c->stream));
-    TRY(dalloc(c, &c->acc, 16));
+    TRY(dalloc(c, &c->acc, 16 + pic::STATS_WORDS));
     TRY(dalloc(c, &c->d_live, 1));
     TRY(dalloc(c, &c->dstate, 1));
     HIP_TRY(c, hipMemsetAsync(c->dstate, 0, sizeof(pic::DevState), c->stream));
@@ -971,7 +971,7 @@ pic_status pic_query_sizes(const pic_grid *grid, int64_t nparticles, const pic_o
                               : 0;
         total += gf == 0 && fused ? bytes(2 * FS + N, 4) : (3 - gf) * bytes(N, 4);
     }
-    total += bytes(1, 4) + bytes(16, 8) + bytes(1, 4) + bytes(1, sizeof(pic::DevState));
+    total += bytes(1, 4) + bytes(16 + pic::STATS_WORDS, 8) + bytes(1, 4) + bytes(1, sizeof(pic::DevState));
     for (int d = 0; d < 3; ++d) {                             // CPML tables and memories
         if (g.bc[d] != PIC_BC_CPML) continue;
         total += bytes(6 * n[d], 4) + 4 * bytes(2LL * g.npml * (N / n[d]), 4);
@@ -1160,15 +1160,8 @@ pic_status pic_stats(pic_ctx *c, pic_stats_out *out)
 {
     CHECK_CTX(c);
     if (!out) return fail(c, PIC_EINVAL, "out is NULL");
-    unsigned long long pushes = 0;
-    HIP_TRY(c, hipStreamSynchronize(c->stream));
-    if (c->n_wave_slots) {
-        std::vector<unsigned long long> slots(c->n_wave_slots);
-        HIP_TRY(c, hipMemcpy(slots.data(), c->d_pushes, 8 * slots.size(), hipMemcpyDeviceToHost));
-        for (unsigned long long v : slots) pushes += v;
-    }
     out->steps = c->step;
-    out->pushes = (int64_t)pushes;
+    out->pushes = 0;
     out->hcur = c->hcur;
     out->device_bytes = (int64_t)c->dev_bytes;
     out->live = 0;
@@ -1177,12 +1170,22 @@ pic_status pic_stats(pic_ctx *c, pic_stats_out *out)
         out->pbox[3 + d] = -1;
     }
     if (c->np > 0) {
-        HIP_TRY(c, hipMemcpy(out->pbox, c->box, sizeof out->pbox, hipMemcpyDeviceToHost));
-        pic_diag_out d;
-        pic_status st = pic_diag(c, &d);
-        if (st != PIC_OK) return st;
-        out->live = (int64_t)d.count;
+        // counted by themselves: the sums of pic_diag over fields and particles took
+        // 70 us or more of a call that needs none of them
+        unsigned long long part[pic::STATS_WORDS];
+        unsigned long long *dev = reinterpret_cast<unsigned long long *>(c->acc + 16);
+        const int nb = pic::launch_stats(diag_args(c), c->d_pushes, (int)c->n_wave_slots, c->box, dev, c->stream);
+        HIP_TRY(c, hipGetLastError());
+        HIP_TRY(c, hipMemcpyAsync(part, dev, sizeof part, hipMemcpyDeviceToHost, c->stream));
+        HIP_TRY(c, hipStreamSynchronize(c->stream));
+        for (int b = 0; b < nb; ++b) {
+            out->live += (int64_t)part[2 * b];
+            out->pushes += (int64_t)part[2 * b + 1];
+        }
+        std::memcpy(out->pbox, part + 2 * pic::STATS_BLOCKS, sizeof out->pbox);
+        return PIC_OK;
     }
+    HIP_TRY(c, hipStreamSynchronize(c->stream));
     return PIC_OK;
 }
 

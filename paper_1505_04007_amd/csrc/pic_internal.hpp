@@ -457,6 +457,13 @@ struct DiagArgs {
 void launch_rho(const DiagArgs &a, hipStream_t s);
 void launch_diag_reduce(const DiagArgs &a, hipStream_t s);
 
+// The particle counters of pic_stats: out[2 b], out[2 b + 1] = live particles and
+// pushes of workgroup b < the number returned, then the box (6 int) at out + 2
+// STATS_BLOCKS.
+constexpr int STATS_BLOCK = 1024, STATS_BLOCKS = 256, STATS_WORDS = 2 * STATS_BLOCKS + 3;
+int launch_stats(const DiagArgs &a, const unsigned long long *pushes, int nslots, const int *box,
+                 unsigned long long *out, hipStream_t s);
+
 // ---- probes ----
 
 // sin and cos of x: x less the nearest multiple n of pi/2 (pi/2 as a sum of two
