@@ -164,7 +164,16 @@ def _f64(a):
 
 def to_compact(arr_xyz):
     """(nx, ny, nz) array -> compact layout (x fastest) as float64."""
-    return _f64(np.asarray(arr_xyz).transpose(2, 1, 0))
+    a = np.asarray(arr_xyz).transpose(2, 1, 0)
+    if a.dtype == np.float64 and a.flags.c_contiguous:
+        return a
+    # 16 x planes at a time: with a whole row's planes in flight every value is a
+    # cache miss where their distance is a power of two (128x64x64: 5.7 -> 0.5 ms,
+    # 512x64x64: 95 -> 2.4 ms)
+    out = np.empty(a.shape)
+    for i in range(0, a.shape[2], 16):
+        out[:, :, i:i + 16] = a[:, :, i:i + 16]
+    return out
 
 
 def from_compact(flat, n):
