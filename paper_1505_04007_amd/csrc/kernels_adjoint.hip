@@ -161,7 +161,7 @@ __device__ __forceinline__ void prep_use(const Prep &r, int q, float *__restrict
 __global__ __launch_bounds__(ADJ_BLOCK) void k_adj_face(AdjArgs a)
 {
     int i, j, k;
-    if (!adj_cell(a, xcd_tile(), i, j, k)) return;
+    if (!adj_cell(a, xcd_tile(blockIdx.x, gridDim.x, a.turns), i, j, k)) return;
     const int id = i + a.nx * (j + a.ny * k);
     bool okx, oky, okz;
     const int ox = nb_off(i, 1, a.nx, a.per[0], 1, okx);
@@ -226,7 +226,7 @@ __global__ __launch_bounds__(ADJ_BLOCK) void k_adj_face(AdjArgs a)
 __global__ __launch_bounds__(ADJ_BLOCK) void k_adj_edge(AdjArgs a)
 {
     int i, j, k;
-    if (!adj_cell(a, xcd_tile(), i, j, k)) return;
+    if (!adj_cell(a, xcd_tile(blockIdx.x, gridDim.x, a.turns), i, j, k)) return;
     const int id = i + a.nx * (j + a.ny * k);
     const bool mx = e_masked<0>(a, i, j, k), my = e_masked<1>(a, i, j, k), mz = e_masked<2>(a, i, j, k);
     const float ex1 = a.Ea[0][id], ey1 = a.Ea[1][id], ez1 = a.Ea[2][id];

@@ -332,8 +332,10 @@ __device__ __forceinline__ void h_front(const ProbeArgs &pr, DevState *state, in
     }
 }
 
-// FRONT: the workgroups in front (0 or XCDS).
-template <int TXW, int TYW, int ZO, int FRONT>
+// FRONT: the workgroups in front (0 or XCDS); TURNS: a.turns is not 0.  Both are
+// known at compile time because a launch on a small grid takes 3 us: with the
+// mapping's two ways in every workgroup a step of 32x32x32 cells took 0.6 us more.
+template <int TXW, int TYW, int ZO, int FRONT, int TURNS>
 __global__ __launch_bounds__(TXW *TYW) void k_h_update(FieldArgs a, ProbeArgs pr)
 {
     const int blk = (int)blockIdx.x - FRONT;
@@ -342,16 +344,16 @@ __global__ __launch_bounds__(TXW *TYW) void k_h_update(FieldArgs a, ProbeArgs pr
         return;
     }
     int i, j, k;
-    if (!tile_cell<TXW, TYW, ZO>(a, xcd_tile(blk, gridDim.x - FRONT), i, j, k)) return;
+    if (!tile_cell<TXW, TYW, ZO>(a, xcd_tile(blk, gridDim.x - FRONT, TURNS ? a.turns : 0), i, j, k)) return;
     const gp<const DevState> st = G(a.st);
     h_cell(a, st->parity, box_margin(st->since_sort, a.S), i, j, k);
 }
 
-template <int TXW, int TYW, int ZO>
+template <int TXW, int TYW, int ZO, int TURNS>
 __global__ __launch_bounds__(TXW *TYW) void k_e_update(FieldArgs a)
 {
     int i, j, k;
-    const bool in = tile_cell<TXW, TYW, ZO>(a, xcd_tile_rev(), i, j, k);
+    const bool in = tile_cell<TXW, TYW, ZO>(a, xcd_tile_rev(TURNS ? a.turns : 0), i, j, k);
     const gp<const DevState> st = G(a.st);
     const int parity = a.tick ? st->e_parity : st->parity, since = a.tick ? st->e_since : st->since_sort;
     if (in) e_cell(a, parity, box_margin(since, a.S), i, j, k);
@@ -365,7 +367,8 @@ __global__ __launch_bounds__(TXW *TYW) void k_e_update(FieldArgs a)
 template <int TXW, int TYW, int ZO>
 __global__ __launch_bounds__(TXW *TYW) void k_h_update_batch(const FieldArgs *__restrict__ args,
                                                              const int *__restrict__ own,
-                                                             const ProbeArgs *__restrict__ probe, int nmem, int extra)
+                                                             const ProbeArgs *__restrict__ probe, int nmem, int extra,
+                                                             int turns)
 {
     const int blk = (int)blockIdx.x - extra;
     if (blk < 0) {
@@ -373,7 +376,7 @@ __global__ __launch_bounds__(TXW *TYW) void k_h_update_batch(const FieldArgs *__
         if (m < nmem) h_front(probe ? probe[m] : ProbeArgs{}, args[m].st, t, TXW * TYW);
         return;
     }
-    const int o = own[xcd_tile(blk, gridDim.x - extra)];
+    const int o = own[xcd_tile(blk, gridDim.x - extra, turns)];
     const FieldArgs &a = args[o >> 24];
     const gp<const DevState> st = G(a.st);
     const int parity = st->parity, margin = box_margin(st->since_sort, a.S);
@@ -386,9 +389,9 @@ __global__ __launch_bounds__(TXW *TYW) void k_h_update_batch(const FieldArgs *__
 
 template <int TXW, int TYW, int ZO>
 __global__ __launch_bounds__(TXW *TYW) void k_e_update_batch(const FieldArgs *__restrict__ args,
-                                                             const int *__restrict__ own)
+                                                             const int *__restrict__ own, int turns)
 {
-    const int o = own[xcd_tile_rev()];
+    const int o = own[xcd_tile_rev(turns)];
     const FieldArgs &a = args[o >> 24];
     const gp<const DevState> st = G(a.st);
     const int parity = a.tick ? st->e_parity : st->parity, since = a.tick ? st->e_since : st->since_sort;
@@ -423,33 +426,40 @@ template <int TXW, int TYW, int ZO>
 struct HLaunch {
     static void launch(int blocks, hipStream_t s, FieldArgs a, ProbeArgs pr)
     {
+        if (a.turns) launch_turns<1>(blocks, s, a, pr);
+        else launch_turns<0>(blocks, s, a, pr);
+    }
+    template <int TURNS>
+    static void launch_turns(int blocks, hipStream_t s, FieldArgs a, ProbeArgs pr)
+    {
         if (a.tick)
-            hipLaunchKernelGGL((k_h_update<TXW, TYW, ZO, XCDS>), dim3(blocks + XCDS), dim3(TXW, TYW), 0, s, a, pr);
+            hipLaunchKernelGGL((k_h_update<TXW, TYW, ZO, XCDS, TURNS>), dim3(blocks + XCDS), dim3(TXW, TYW), 0, s, a, pr);
         else
-            hipLaunchKernelGGL((k_h_update<TXW, TYW, ZO, 0>), dim3(blocks), dim3(TXW, TYW), 0, s, a, pr);
+            hipLaunchKernelGGL((k_h_update<TXW, TYW, ZO, 0, TURNS>), dim3(blocks), dim3(TXW, TYW), 0, s, a, pr);
     }
 };
 template <int TXW, int TYW, int ZO>
 struct ELaunch {
     static void launch(int blocks, hipStream_t s, FieldArgs a)
     {
-        hipLaunchKernelGGL((k_e_update<TXW, TYW, ZO>), dim3(blocks), dim3(TXW, TYW), 0, s, a);
+        if (a.turns) hipLaunchKernelGGL((k_e_update<TXW, TYW, ZO, 1>), dim3(blocks), dim3(TXW, TYW), 0, s, a);
+        else hipLaunchKernelGGL((k_e_update<TXW, TYW, ZO, 0>), dim3(blocks), dim3(TXW, TYW), 0, s, a);
     }
 };
 template <int TXW, int TYW, int ZO>
 struct HBatchLaunch {
     static void launch(int blocks, hipStream_t s, const FieldArgs *args, const int *own, const ProbeArgs *probe,
-                       int nmem, int extra)
+                       int nmem, int extra, int turns)
     {
         hipLaunchKernelGGL((k_h_update_batch<TXW, TYW, ZO>), dim3(blocks), dim3(TXW, TYW), 0, s, args, own, probe,
-                           nmem, extra);
+                           nmem, extra, turns);
     }
 };
 template <int TXW, int TYW, int ZO>
 struct EBatchLaunch {
-    static void launch(int blocks, hipStream_t s, const FieldArgs *args, const int *own)
+    static void launch(int blocks, hipStream_t s, const FieldArgs *args, const int *own, int turns)
     {
-        hipLaunchKernelGGL((k_e_update_batch<TXW, TYW, ZO>), dim3(blocks), dim3(TXW, TYW), 0, s, args, own);
+        hipLaunchKernelGGL((k_e_update_batch<TXW, TYW, ZO>), dim3(blocks), dim3(TXW, TYW), 0, s, args, own, turns);
     }
 };
 
@@ -467,12 +477,12 @@ void launch_h_update_batch(const FieldArgs *args, const int *own, int total, int
                            int nmem, hipStream_t s)
 {
     const int extra = (nmem + XCDS - 1) / XCDS * XCDS;
-    launch_shape<HBatchLaunch>(shape, total + extra, s, args, own, probe, nmem, extra);
+    launch_shape<HBatchLaunch>(shape, total + extra, s, args, own, probe, nmem, extra, xcd_turns(total));
 }
 
 void launch_e_update_batch(const FieldArgs *args, const int *own, int total, int shape, hipStream_t s)
 {
-    launch_shape<EBatchLaunch>(shape, total, s, args, own);
+    launch_shape<EBatchLaunch>(shape, total, s, args, own, xcd_turns(total));
 }
 
 }  // namespace pic

@@ -93,7 +93,7 @@ __global__ __launch_bounds__(1024) void k_fused(FusedArgs a)
     const int i = threadIdx.x;
     const bool xin = i < a.nx;
     const int ic = xin ? i : a.nx - 1;  // inactive lanes load a valid cell and store nothing
-    const int u = xcd_tile();
+    const int u = xcd_block(blockIdx.x, gridDim.x);
     const int j0 = (u % a.gy) * R, k0 = (u / a.gy) * FUSED_PLANES;
     const int nplanes = min(FUSED_PLANES, a.nz - k0);
     const int nx = a.nx, ny = a.ny, nz = a.nz, N = a.N;

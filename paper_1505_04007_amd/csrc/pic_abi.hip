@@ -98,7 +98,6 @@ void build_args(pic_ctx *c)
     a.nx = c->n[0];
     a.ny = c->n[1];
     a.nz = c->n[2];
-    pic::set_tile(a, c->tile);
     a.S = (float)c->S;
     for (int d = 0; d < 3; ++d) {
         a.per[d] = c->per[d];
@@ -113,6 +112,7 @@ void build_args(pic_ctx *c)
         a.Jb[d] = c->Jb[d];
         a.Jq[d] = c->Jq[d];
     }
+    pic::set_tile(a, c->tile);
     a.qinv = c->qinv;
     a.coef = c->coef;
     a.pbox = c->np > 0 ? c->box : nullptr;

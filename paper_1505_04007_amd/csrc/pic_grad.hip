@@ -301,6 +301,7 @@ pic_status grad_impl(pic_ctx *c, GradScratch &g, double omega0, long long N, lon
     aa.nz = c->n[2];
     aa.dx = pic::make_div(c->n[0]);
     aa.dy = pic::make_div(c->n[1]);
+    aa.turns = pic::xcd_turns(pic::field_tiles(aa.nx, aa.ny, aa.nz, pic::TILE_RUNS), aa.nz, c->pml[2]);
     aa.S = (float)c->S;
     for (int d = 0; d < 3; ++d) {
         aa.per[d] = c->per[d];

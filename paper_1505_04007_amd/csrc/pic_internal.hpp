@@ -133,6 +133,7 @@ struct FieldArgs {
     int *nan_flag;
     int tick;         // the field updates move the clock (0: the probe launch does, or nothing)
     DevState *st;
+    int turns;        // tiles of an XCD that it takes in turns with the others (xcd_turns)
 };
 
 // One-pass field sweep (E update of step n, then H update of step n + 1).
@@ -265,6 +266,25 @@ inline int field_tiles(int nx, int ny, int nz, int shape = 0)
 // 448x128x128 125.7 / 114.3 / 126.1, 512x256x256 591 / 556 / 615.
 inline int default_tile(int nx, int ny) { return (long long)nx * ny > (1 << 15) ? TILE_BAND_RUNS : TILE_RUNS; }
 
+// How the 8 XCDs share the tiles.  A contiguous block each keeps a block's
+// neighbour planes in one L2, but the first and the last then have the absorbing
+// slabs of the axis that the order goes through last (and one has the metal film)
+// to themselves, and the others wait for them.  So where those slabs fill a quarter
+// of such a block or more, the XCDs take turns at chunks of 16 tiles.  H + E pair
+// and adjoint pair, blocks / turns: 301x203x157 172.5 / 162.2 us, 512x256x256 565 /
+// 548, a batch of 16 of 176x64x64 and up 381 / 361, 128x64x64 15.3 / 15.2 and 26.0 /
+// 21.8; but 281x1x3601 with slabs of 10 of 450 planes 19.0 / 20.8, 96x64x96 without
+// slabs 17.2 / 17.8, 91x45x53 (848 tiles) 10.0 / 10.2 and 12.4 / 12.6.  Chunks of 11,
+// 16, 19, 32, 43, 64 tiles on 512x256x256: 609, 547, 601, 598, 589, 572 (16 is half
+// a band's plane there), on 301x203x157 161.6 to 162.3.
+constexpr int XCD_CHUNK = 16;
+inline int xcd_turns(long long tiles) { return (int)(tiles / (8 * XCD_CHUNK)) * XCD_CHUNK; }
+inline int xcd_turns(long long tiles, int n, const PmlAxis &slow)
+{
+    return tiles >= 1024 && slow.on && 32LL * slow.npml >= n ? xcd_turns(tiles) : 0;
+}
+
+// (a's sizes and slabs are set)
 inline void set_tile(FieldArgs &a, int shape)
 {
     a.tile = shape;
@@ -273,6 +293,8 @@ inline void set_tile(FieldArgs &a, int shape)
     a.dx = make_div(runs || band ? a.nx : a.gx);
     a.dy = make_div(runs ? a.ny : band ? a.gx : a.gy);
     a.dz = make_div(a.nz);
+    const int slow = TILE_ZO[shape] ? 1 : 2;
+    a.turns = xcd_turns(field_tiles(a.nx, a.ny, a.nz, shape), slow == 1 ? a.ny : a.nz, a.pml[slow]);
 }
 
 // Work units of one member in a batched field launch.
@@ -345,22 +367,29 @@ __device__ __forceinline__ void gatomic_add(gp<unsigned long long> p, unsigned l
 // Workgroup b of B -> tile with XCD locality: the 8 XCDs receive workgroups
 // round robin, so workgroup b runs on XCD b % 8; give each XCD a contiguous
 // block of tiles.
-__device__ __forceinline__ int xcd_tile(int b, int B)
+__device__ __forceinline__ int xcd_block(int b, int B)
 {
     const int x = b & 7, q = B >> 3, r = B & 7;
     return x * q + min(x, r) + (b >> 3);
 }
-__device__ __forceinline__ int xcd_tile() { return xcd_tile(blockIdx.x, gridDim.x); }
 
-// xcd_tile() with each XCD walking its range from the end: a launch that
+// The same with the first `turns` tiles of every XCD in chunks of XCD_CHUNK, the
+// XCDs taking turns (xcd_turns).
+__device__ __forceinline__ int xcd_tile(int b, int B, int turns)
+{
+    const int x = b & 7, i = b >> 3;
+    if (i < turns) return (i / XCD_CHUNK * 8 + x) * XCD_CHUNK + i % XCD_CHUNK;
+    return 8 * turns + xcd_block(b - 8 * turns, B - 8 * turns);
+}
+
+// xcd_tile() with each XCD walking its tiles from the end: a launch that
 // follows one in the forward order starts on the tiles the other wrote last,
 // which are still in the Infinity Cache.
-__device__ __forceinline__ int xcd_tile_rev()
+__device__ __forceinline__ int xcd_tile_rev(int turns)
 {
-    const int B = gridDim.x, b = blockIdx.x;
-    const int x = b & 7, i = b >> 3, q = B >> 3, r = B & 7;
-    const int len = q + (x < r ? 1 : 0);
-    return x * q + min(x, r) + (len - 1 - i);
+    const int B = gridDim.x, x = blockIdx.x & 7, i = blockIdx.x >> 3;
+    const int len = (B >> 3) + (x < (B & 7) ? 1 : 0);
+    return xcd_tile(8 * (len - 1 - i) + x, B, turns);
 }
 
 // Position of plane q inside the two absorbing slabs of an axis.
@@ -406,6 +435,7 @@ void launch_probe_batch(const ProbeArgs *args, int n, hipStream_t s);
 struct AdjArgs {
     int nx, ny, nz;
     Div dx, dy;  // division by nx and ny: one thread per cell, in memory order
+    int turns;   // as in FieldArgs
     int per[3];
     float S;
     float *Ea[3];
