@@ -16,10 +16,9 @@
 // wavefront mostly share a grid row: the sum over the particles of a row is a
 // small matrix product (x factors times transverse factors) and runs on the
 // matrix cores in FP32 (deposit_rows).  Rows with few lanes use per-lane
-// atomics.  Few particles are spread over more wavefronts (k_push_split).  The fixed-point deposit sums integers instead: lanes with equal
-// windows by recursive halving (64 slots -> one slot per lane), the two widest
-// exchanges by the gfx950 half-wave swaps (v_permlane32_swap,
-// v_permlane16_swap), the four narrow ones by DPP lane moves.
+// atomics.  Few particles are spread over more wavefronts (k_push_split).  The
+// fixed-point deposit sums integers, exactly, as signed bytes on the matrix
+// cores (deposit_fixed).
 #include "pic_internal.hpp"
 
 namespace pic {
@@ -245,64 +244,11 @@ __device__ __forceinline__ int slot_index(const PartArgs &a, int s, int bx, int 
 // Fixed-point deposit: each particle's slot currents are rounded to integer
 // units (qscale per V/m, at most 2^24 per slot) before anything is summed, so
 // the wavefront sums (at most 2^30) and the 64-bit atomics are exact and the
-// result does not depend on which lanes share a round or on atomic order.
+// result does not depend on which lanes are summed together or on atomic order.
 __device__ __forceinline__ void add_fixed(const PartArgs &a, int comp, int q, int units)
 {
     unsigned long long *J = comp == 0 ? a.Jq[0] : (comp == 1 ? a.Jq[1] : a.Jq[2]);
     gatomic_add(G(J) + q, (unsigned long long)(long long)units);
-}
-
-// Lane l receives x from lane l ^ OFF (OFF = 8, 4, 2, 1), by DPP row moves.
-template <int OFF>
-__device__ __forceinline__ int xor_lane(int v)
-{
-    if (OFF == 8) return __builtin_amdgcn_update_dpp(0, v, 0x128, 0xf, 0xf, false);  // row_ror:8
-    if (OFF == 4) {
-        // lanes with bit 2 clear (banks 0, 2) read l + 4, the others l - 4
-        const int t = __builtin_amdgcn_update_dpp(0, v, 0x104, 0xf, 0x5, false);  // row_shl:4
-        return __builtin_amdgcn_update_dpp(t, v, 0x114, 0xf, 0xa, false);         // row_shr:4
-    }
-    if (OFF == 2) return __builtin_amdgcn_update_dpp(0, v, 0x4e, 0xf, 0xf, false);  // quad_perm [2,3,0,1]
-    return __builtin_amdgcn_update_dpp(0, v, 0xb1, 0xf, 0xf, false);                // quad_perm [1,0,3,2]
-}
-
-template <int OFF>
-__device__ __forceinline__ void halve_dpp(int *v, int lane)
-{
-    const bool up = (lane & OFF) != 0;
-#pragma unroll
-    for (int e = 0; e < OFF; ++e) {
-        const int send = up ? v[e] : v[e + OFF];
-        const int keep = up ? v[e + OFF] : v[e];
-        v[e] = keep + xor_lane<OFF>(send);
-    }
-}
-
-// Sum of the lanes' 54 fixed-point slot currents over the lanes with `mine`
-// set: lane l ends with slot l.  Rounds of width 32 and 16: the lower half-wave
-// keeps slot e, the upper keeps slot e + OFF; a half-wave swap of the two
-// registers puts each half's partner values next to its own, and the sum
-// finishes the round.  The first round reads zeros for a lane outside.
-__device__ __forceinline__ int wave_reduce64(const int *val, bool mine, int lane)
-{
-    int v[32];
-#pragma unroll
-    for (int e = 0; e < 32; ++e) {
-        const int lo = mine ? val[e] : 0;
-        const int hi = (e + 32 < 54 && mine) ? val[e + 32 < 54 ? e + 32 : 0] : 0;
-        const auto r = __builtin_amdgcn_permlane32_swap((unsigned)lo, (unsigned)hi, false, false);
-        v[e] = (int)(r[0] + r[1]);
-    }
-#pragma unroll
-    for (int e = 0; e < 16; ++e) {
-        const auto r = __builtin_amdgcn_permlane16_swap((unsigned)v[e], (unsigned)v[e + 16], false, false);
-        v[e] = (int)(r[0] + r[1]);
-    }
-    halve_dpp<8>(v, lane);
-    halve_dpp<4>(v, lane);
-    halve_dpp<2>(v, lane);
-    halve_dpp<1>(v, lane);
-    return v[0];
 }
 
 // Where the three nodes of a window along one axis are stored: linear offsets,
@@ -543,11 +489,117 @@ __device__ __forceinline__ bool leaves(const PartArgs &a, float x, float y, floa
            (!a.per[1] && !(y >= 0.f && y < (float)a.ny)) || (!a.per[2] && !(z >= 0.f && z < (float)a.nz));
 }
 
-// Fixed-point deposit: a window shared by at least ROUND_LANES lanes is summed
-// by a wavefront round (about 220 VALU instructions, then one atomic per slot);
-// the lanes of smaller windows add their slots with per-lane atomics, all such
-// lanes of the wavefront together (54 atomic instructions however many lanes).
-constexpr int ROUND_LANES = 3;
+// ---- fixed-point deposit (matrix cores on bytes) ----
+// The sums over the particles of every window of a wavefront are a matrix product:
+// 16 windows by 64 particles (1 where the particle has the window) times 64 particles
+// by 16 slots, 4 such products for the 54 slots.  A slot's units are split into
+// 4 signed bytes, v_mfma_i32_16x16x64_i8 sums each byte exactly, and the sums are
+// put together again (at most 2^30).  Lane l holds row or column l % 16 of the
+// particles 16 (l / 16) on; the units get there from their particle's lane through
+// LDS, 16 slots at a time.  Summing windows one after another, with 220 VALU
+// instructions each, and their short ones with 54 atomics per lane, took 30.1 us for
+// 2e5 particles in 96x64x96 cells, now 24.2 (2e4: 20.3 -> 19.5, 1e6: 59.1 -> 57.1);
+// what is left is the 54 units of every particle and the gather.
+typedef int ivec4 __attribute__((ext_vector_type(4)));
+struct FixLds {
+    int units[16][68];  // by slot (rows that 16 lanes read at once start 4 banks apart), by particle
+    int base[3][64];
+};
+
+// The bytes of 4 dwords, transposed: dword b of the result is byte b of each.
+__device__ __forceinline__ ivec4 byte_planes(ivec4 v)
+{
+    const unsigned lo01 = __builtin_amdgcn_perm(v.y, v.x, 0x05010400), hi01 = __builtin_amdgcn_perm(v.y, v.x, 0x07030602);
+    const unsigned lo23 = __builtin_amdgcn_perm(v.w, v.z, 0x05010400), hi23 = __builtin_amdgcn_perm(v.w, v.z, 0x07030602);
+    return ivec4{(int)__builtin_amdgcn_perm(lo23, lo01, 0x05040100), (int)__builtin_amdgcn_perm(lo23, lo01, 0x07060302),
+                 (int)__builtin_amdgcn_perm(hi23, hi01, 0x05040100), (int)__builtin_amdgcn_perm(hi23, hi01, 0x07060302)};
+}
+
+template <class Units>
+__device__ __forceinline__ void deposit_fixed(const PartArgs &a, FixLds &L, unsigned long long rem, int lane,
+                                              const int base[3], Units units)
+{
+    const int n = lane & 15, q = lane >> 4;
+#pragma unroll
+    for (int d = 0; d < 3; ++d) L.base[d][lane] = base[d];
+    ivec4 B[4][4];  // by 16 slots, by byte
+#pragma unroll
+    for (int T = 0; T < 4; ++T) {
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int s = 16 * T; s < (T < 3 ? 16 * T + 16 : 54); ++s)
+            L.units[s - 16 * T][lane] = (units(s) + 0x808080) ^ 0x808080;  // signed bytes
+        __builtin_amdgcn_wave_barrier();
+        ivec4 p[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            p[e] = byte_planes(*reinterpret_cast<const ivec4 *>(&L.units[T < 3 ? n : min(n, 5)][16 * q + 4 * e]));
+#pragma unroll
+        for (int b = 0; b < 4; ++b) B[T][b] = ivec4{p[0][b], p[1][b], p[2][b], p[3][b]};
+    }
+    const int key = (base[0] + 1) + (a.nx + 2) * ((base[1] + 1) + (a.ny + 2) * (base[2] + 1));
+    // the window's first cell where the window is inside the grid, else -1
+    const bool in = base[0] >= 0 && base[0] + 2 < a.nx && base[1] >= 0 && base[1] + 2 < a.ny && base[2] >= 0 &&
+                    base[2] + 2 < a.nz;
+    const int first = in ? base[0] + a.nx * (base[1] + a.ny * base[2]) : -1;
+    int rel[4];
+    unsigned long long *J[4];
+#pragma unroll
+    for (int T = 0; T < 4; ++T) {
+        int comp, oi, oj, ok;
+        slot_geom(min(16 * T + n, 53), comp, oi, oj, ok);
+        rel[T] = oi + a.nx * (oj + a.ny * ok);
+        J[T] = comp == 0 ? a.Jq[0] : (comp == 1 ? a.Jq[1] : a.Jq[2]);
+    }
+    while (rem) {
+        // up to 16 windows: w in row 4 (w % 4) + w / 4, so that few of them lie in
+        // the first results of all lanes; lead: the lanes windows 4 j + q lead
+        unsigned long long mine = 0;
+        int lead[4] = {0, 0, 0, 0}, w = 0;
+        for (; w < 16 && rem; ++w) {
+            const int leader = __ffsll((long long)rem) - 1;
+            const unsigned long long m = __ballot(key == __builtin_amdgcn_readlane(key, leader)) & rem;
+            rem &= ~m;
+            if (n == 4 * (w & 3) + (w >> 2)) mine = m;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) lead[j] = w == 4 * j + q ? leader : lead[j];
+        }
+        const unsigned own = (unsigned)(mine >> (16 * q)) & 0xffffu;
+        ivec4 A;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) A[e] = (int)((((own >> (4 * e)) & 15u) * 0x204081u) & 0x01010101u);
+        int at[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) at[j] = __builtin_amdgcn_ds_bpermute(4 * lead[j], first);
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            if (4 * j + q >= w) at[j] = -2;
+#pragma unroll
+        for (int T = 0; T < 4; ++T) {
+            const ivec4 zero = {0, 0, 0, 0};
+            const ivec4 s0 = __builtin_amdgcn_mfma_i32_16x16x64_i8(A, B[T][0], zero, 0, 0, 0);
+            const ivec4 s1 = __builtin_amdgcn_mfma_i32_16x16x64_i8(A, B[T][1], zero, 0, 0, 0);
+            const ivec4 s2 = __builtin_amdgcn_mfma_i32_16x16x64_i8(A, B[T][2], zero, 0, 0, 0);
+            const ivec4 s3 = __builtin_amdgcn_mfma_i32_16x16x64_i8(A, B[T][3], zero, 0, 0, 0);
+            const int s = 16 * T + n;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                if (4 * j >= w) continue;
+                const int tot = (int)((unsigned)s0[j] + ((unsigned)s1[j] << 8) + ((unsigned)s2[j] << 16) +
+                                      ((unsigned)s3[j] << 24));
+                if (s >= 54 || tot == 0) continue;
+                if (at[j] >= 0) {
+                    gatomic_add(G(J[T]) + (at[j] + rel[T]), (unsigned long long)(long long)tot);
+                } else if (at[j] == -1) {  // the window wraps or leaves the grid
+                    const int p = lead[j];
+                    int comp;
+                    const int cell = slot_index(a, s, L.base[0][p], L.base[1][p], L.base[2][p], comp);
+                    if (cell >= 0) add_fixed(a, comp, cell, tot);
+                }
+            }
+        }
+    }
+}
 
 // The passes of a wavefront's rows with at least ROW_LANES lanes; the lanes left over.
 __device__ __forceinline__ unsigned long long row_passes(const PartArgs &a, RowLds &L, unsigned long long rem,
@@ -661,45 +713,13 @@ __device__ __forceinline__ void push_body(const PartArgs &a, int blk)
     unsigned long long rem = live;
     if (!live) return;
     if (FIX) {
-        // integer units per slot (0 for a lane that does not deposit), each
-        // computed once whichever way it is added: the sums do not depend on
-        // which lanes share a round
+        // integer units per slot, each computed once: the sums do not depend on
+        // which lanes are summed together
+        __shared__ FixLds L;
         const AxisF fx = axis_factors(x0, x1, base[0]), fy = axis_factors(y0, y1, base[1]),
                     fz = axis_factors(z0, z1, base[2]);
-        int val[54];
-#pragma unroll
-        for (int s = 0; s < 54; ++s) val[s] = __float2int_rn(a.qd * slot_value(fx, fy, fz, s) * a.qscale);
-        // lane l < 54 owns slot l of every round's window: its component and
-        // offset from the window's base node, computed once
-        int lc, li, lj, lk;
-        slot_geom(lane < 54 ? lane : 0, lc, li, lj, lk);
-        const int lrel = li + a.nx * (lj + a.ny * lk);
-        const int key = (base[0] + 1) + (a.nx + 2) * ((base[1] + 1) + (a.ny + 2) * (base[2] + 1));
-        unsigned long long small = 0;
-        while (rem) {
-            const int leader = __ffsll((long long)rem) - 1;
-            const int k0 = __builtin_amdgcn_readlane(key, leader);
-            const bool mine = ((rem >> lane) & 1ull) && key == k0;
-            const unsigned long long m = __ballot(mine);
-            rem &= ~m;
-            if (__popcll(m) < ROUND_LANES) {
-                small |= m;
-                continue;
-            }
-            const int tot = wave_reduce64(val, mine, lane);
-            const int bx = __builtin_amdgcn_readlane(base[0], leader);
-            const int by = __builtin_amdgcn_readlane(base[1], leader);
-            const int bz = __builtin_amdgcn_readlane(base[2], leader);
-            if (lane < 54 && tot != 0) {
-                const bool inside = bx >= 0 && bx + 2 < a.nx && by >= 0 && by + 2 < a.ny && bz >= 0 && bz + 2 < a.nz;
-                int comp = lc;
-                const int q = inside ? (bx + a.nx * (by + a.ny * bz)) + lrel : slot_index(a, lane, bx, by, bz, comp);
-                if (q >= 0) add_fixed(a, comp, q, tot);
-            }
-        }
-        if ((small >> lane) & 1ull)
-            lane_deposit(a, base, [&](int s) { return val[s]; },
-                         [&](int comp, int q, int u) { add_fixed(a, comp, q, u); });
+        deposit_fixed(a, L, rem, lane, base,
+                      [&](int s) { return __float2int_rn(a.qd * slot_value(fx, fy, fz, s) * a.qscale); });
         return;
     }
     if (MODE == 0) {
