@@ -1,11 +1,9 @@
 // Yee curl updates for gfx950: H update (vacuum form) and the fused Drude
 // polarization-current + E update.
 //
-// One thread per cell, one workgroup per run of 256 cells in memory order or per
-// (x, y) tile of one z plane (default_tile's rule; the autotuner picks another
-// shape from a fixed table per grid), x fastest so a wavefront reads contiguous
-// rows.  Each
-// cell reads its own three old values and the three neighbour values its
+// One thread per cell, one workgroup per run of 256 cells in memory order (the
+// autotuner may pick another shape, as (x, y) tiles of one z plane, from a fixed
+// table), x fastest so a wavefront reads contiguous rows.  Each cell reads its own three old values and the three neighbour values its
 // curl needs (+x/+y/+z for H, -x/-y/-z for E); the neighbours are the own
 // values of adjacent lanes, rows and planes and are served by L1/L2, so the
 // HBM traffic stays close to one read and one write of every array.

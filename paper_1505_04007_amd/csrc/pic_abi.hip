@@ -571,7 +571,7 @@ static pic_status init_impl(pic_ctx *c, const pic_grid *grid, double dx, double 
         return fail(c, PIC_EINVAL, "wp_map / gamma_map must be finite and >= 0");
     c->dx = dx;
     c->dt = dt;
-    c->tile = pic::default_tile(nn[0], nn[1]);
+    c->tile = pic::DEFAULT_TILE;
     c->S = kC * dt / dx;
     double wpmax = 0.0;
     for (long long q = 0; q < ncell; ++q) wpmax = std::max(wpmax, wp_map[q]);

@@ -135,15 +135,6 @@ pic_status batch_upload_fields(pic_batch *b, int shape, bool tick = true)
     return PIC_OK;
 }
 
-// The default shape of the members' largest plane (one shape for all).
-int batch_default_tile(const pic_batch *b)
-{
-    int t = pic::TILE_RUNS;
-    for (const pic_ctx *c : b->ctx)
-        if (pic::default_tile(c->n[0], c->n[1]) == pic::TILE_BAND_RUNS) t = pic::TILE_BAND_RUNS;
-    return t;
-}
-
 // Capture one sort period (sort_every steps, then the sorts; since_sort is 0
 // at the start of every replay); fields-only batches capture 10 steps.
 pic_status batch_capture(pic_batch *b)
@@ -236,7 +227,7 @@ static pic_status batch_create_impl(pic_batch *b, pic_ctx *const *ctxs, int32_t 
         b->tiles_cap = std::max(b->tiles_cap, (size_t)t);
     }
     BHIP(b, hipMalloc(&b->d_tiles, sizeof(int) * std::max<size_t>(b->tiles_cap, 1)));
-    pic_status st = batch_upload_fields(b, batch_default_tile(b));
+    pic_status st = batch_upload_fields(b, pic::DEFAULT_TILE);
     if (st != PIC_OK) return st;
     BHIP(b, hipMemcpy(b->d_pa, pa.data(), sizeof(pic::PartArgs) * n, hipMemcpyHostToDevice));
     BHIP(b, hipMemcpy(b->d_pr, pr.data(), sizeof(pic::ProbeArgs) * n, hipMemcpyHostToDevice));
@@ -369,7 +360,7 @@ pic_status pic_batch_tune(pic_batch *b, int32_t reps, int32_t force, pic_tune_ou
         (void)hipStreamSynchronize(b->ext);
         for (void *p : saved) (void)hipFree(p);
         if (st != PIC_OK) return st;
-        best = pick_shape(res.ms, batch_default_tile(b));
+        best = pick_shape(res.ms, pic::DEFAULT_TILE);
     }
     pic_status st = batch_upload_fields(b, best);
     if (st != PIC_OK) return st;

@@ -301,7 +301,8 @@ pic_status grad_impl(pic_ctx *c, GradScratch &g, double omega0, long long N, lon
     aa.nz = c->n[2];
     aa.dx = pic::make_div(c->n[0]);
     aa.dy = pic::make_div(c->n[1]);
-    aa.turns = pic::xcd_turns(pic::field_tiles(aa.nx, aa.ny, aa.nz, pic::TILE_RUNS), aa.nz, c->pml[2]);
+    aa.turns = pic::xcd_turns(pic::field_tiles(aa.nx, aa.ny, aa.nz, pic::TILE_RUNS), (long long)aa.nx * aa.ny, aa.nz,
+                              c->pml[2]);
     aa.S = (float)c->S;
     for (int d = 0; d < 3; ++d) {
         aa.per[d] = c->per[d];
@@ -562,7 +563,7 @@ pic_status pic_tune(pic_ctx *c, int32_t reps, int32_t force, pic_tune_out *out)
         HIP_TRY(c, hipStreamSynchronize(c->stream));
         pic_status st = tune_fields(c, reps, res.ms);
         if (st != PIC_OK) return st;
-        c->tile = pick_shape(res.ms, pic::default_tile(c->n[0], c->n[1]));
+        c->tile = pick_shape(res.ms, pic::DEFAULT_TILE);
     }
     build_args(c);
     res.tile = c->tile;

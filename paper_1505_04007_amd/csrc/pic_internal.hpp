@@ -258,30 +258,34 @@ inline int field_tiles(int nx, int ny, int nz, int shape = 0)
 }
 
 // The shape a grid gets before any tuning.  Runs of memory order leave no lane
-// idle at the ends of rows and load aligned; they go through the grid plane by
-// plane up to 2^15 cells a plane and band by band above, where a plane (36 bytes
-// a cell and kernel) would no longer stay in L2 until the next needs it.  H + E
-// launch pair, plane runs / band runs / 64 x 4 cells: 281x1x3601 cells 23.3 /
-// 29.2 / 29.3 us, 91x45x53 7.7 / 10.0 / 8.3, 208x80x80 28.8 / 28.2 / 35.0,
-// 448x128x128 125.7 / 114.3 / 126.1, 512x256x256 591 / 556 / 615.
-inline int default_tile(int nx, int ny) { return (long long)nx * ny > (1 << 15) ? TILE_BAND_RUNS : TILE_RUNS; }
+// idle at the ends of rows and load aligned, and plane by plane the XCDs keep a
+// large plane's values between them (xcd_turns).  H + E launch pair, plane runs /
+// band runs / 64 x 4 cells: 281x1x3601 cells 17.9 / 24.8 / 25.9 us, 91x45x53 7.9 /
+// 8.1 / 9.0, 208x80x80 27.7 / 27.5 / 32.4, 301x203x157 144.7 / 165.8 / 162.9,
+// 448x128x128 104.9 / 112.0 / 107.3, 512x256x256 504 / 513 / 519.
+constexpr int DEFAULT_TILE = TILE_RUNS;
 
 // How the 8 XCDs share the tiles.  A contiguous block each keeps a block's
 // neighbour planes in one L2, but the first and the last then have the absorbing
 // slabs of the axis that the order goes through last (and one has the metal film)
 // to themselves, and the others wait for them.  So where those slabs fill a quarter
-// of such a block or more, the XCDs take turns at chunks of 16 tiles.  H + E pair
-// and adjoint pair, blocks / turns: 301x203x157 172.5 / 162.2 us, 512x256x256 565 /
-// 548, a batch of 16 of 176x64x64 and up 381 / 361, 128x64x64 15.3 / 15.2 and 26.0 /
-// 21.8; but 281x1x3601 with slabs of 10 of 450 planes 19.0 / 20.8, 96x64x96 without
-// slabs 17.2 / 17.8, 91x45x53 (848 tiles) 10.0 / 10.2 and 12.4 / 12.6.  Chunks of 11,
-// 16, 19, 32, 43, 64 tiles on 512x256x256: 609, 547, 601, 598, 589, 572 (16 is half
-// a band's plane there), on 301x203x157 161.6 to 162.3.
+// of such a block or more, the XCDs take turns at chunks of 16 tiles.  They also do
+// plane by plane above 2^15 cells a plane, where one plane of 36 bytes a cell no
+// longer stays in one L2 but, shared by turns, does in all eight.
+// H + E pair and adjoint pair, blocks / turns, order by plane: a batch of 16 of
+// 176x64x64 and up 381 / 361 us, 128x64x64 15.3 / 15.2 and 26.0 / 21.8; but 281x1x3601
+// with slabs of 10 of 450 planes 19.0 / 20.8, 96x64x96 without slabs 17.2 / 17.8,
+// 91x45x53 (848 tiles) 10.0 / 10.2 and 12.4 / 12.6.  Large planes, band runs in
+// blocks / plane runs by turns, no slabs: 512x256x256 436 / 404, 301x203x157 145.7 /
+// 128.5, 200x200x600 333 / 274, 448x128x128 88.8 / 92.4; all slabs: 553 / 504
+// (bands by turns 513), 172.5 / 144.7, (by turns) 368 / 311, 114.3 / 104.9.
+// Band runs by turns of 11, 16, 19, 32, 43, 64 tiles on 512x256x256: 609, 547, 601,
+// 598, 589, 572 (16 is half a band's plane there).
 constexpr int XCD_CHUNK = 16;
 inline int xcd_turns(long long tiles) { return (int)(tiles / (8 * XCD_CHUNK)) * XCD_CHUNK; }
-inline int xcd_turns(long long tiles, int n, const PmlAxis &slow)
+inline int xcd_turns(long long tiles, long long plane, int n, const PmlAxis &slow)
 {
-    return tiles >= 1024 && slow.on && 32LL * slow.npml >= n ? xcd_turns(tiles) : 0;
+    return tiles >= 1024 && (plane > (1 << 15) || (slow.on && 32LL * slow.npml >= n)) ? xcd_turns(tiles) : 0;
 }
 
 // (a's sizes and slabs are set)
@@ -294,7 +298,8 @@ inline void set_tile(FieldArgs &a, int shape)
     a.dy = make_div(runs ? a.ny : band ? a.gx : a.gy);
     a.dz = make_div(a.nz);
     const int slow = TILE_ZO[shape] ? 1 : 2;
-    a.turns = xcd_turns(field_tiles(a.nx, a.ny, a.nz, shape), slow == 1 ? a.ny : a.nz, a.pml[slow]);
+    a.turns = xcd_turns(field_tiles(a.nx, a.ny, a.nz, shape), slow == 1 ? 0 : (long long)a.nx * a.ny,
+                        slow == 1 ? a.ny : a.nz, a.pml[slow]);
 }
 
 // Work units of one member in a batched field launch.

@@ -1,5 +1,6 @@
 """Field and adjoint kernels with the XCDs taking turns at chunks of tiles: from
-1024 tiles on where the last axis of the order has absorbing slabs.  The map from
+1024 tiles on where the last axis of the order has absorbing slabs or a plane is
+large.  The map from
 workgroups to tiles is a permutation that must reach every cell once, at whole
 rounds of 8 chunks and with any remainder; the same cells in tiles of 512 (fewer
 than 1024 of them) are updated in contiguous blocks, with the same arithmetic, so E, H
@@ -23,6 +24,7 @@ P, C = native.BC_PERIODIC, native.BC_CPML
     ((61, 67, 65), (C, C, C)),     # 1038 and a ragged last run
     ((64, 80, 71), (P, C, P)),     # the slabs along y: turns for bands only
     ((128, 72, 64), (C, C, C)),    # 2304 = 2 rounds and 256
+    ((256, 132, 10), (P, P, P)),   # planes above 2^15 cells, no slabs
 ])
 def test_turns_equal_blocks(n, bc):
     rng = np.random.default_rng(sum(n))
