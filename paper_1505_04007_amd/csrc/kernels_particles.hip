@@ -502,7 +502,7 @@ __device__ __forceinline__ bool leaves(const PartArgs &a, float x, float y, floa
 // what is left is the 54 units of every particle and the gather.
 typedef int ivec4 __attribute__((ext_vector_type(4)));
 struct FixLds {
-    int units[16][68];  // by slot (rows that 16 lanes read at once start 4 banks apart), by particle
+    alignas(16) int units[16][68];  // by slot (rows that 16 lanes read at once start 4 banks apart), by particle
     int base[3][64];
 };
 
