@@ -392,7 +392,10 @@ pic_status pic_batch_step(pic_batch *batch, int64_t nsteps);
 /*
  * The autotuner for a batch: one tile shape for all members' field launches
  * (the batched H and E kernels), timed like pic_tune over the whole batch
- * with every member's state restored; re-captures the batch's graph.
+ * with every member's state restored; re-captures the batch's graph.  After an
+ * error the batch keeps the shape it had (a member with 2^24 or more tiles of some
+ * shape gives PIC_EINVAL); should that fail as well, pic_batch_step returns
+ * PIC_ESTATE.
  */
 pic_status pic_batch_tune(pic_batch *b, int32_t reps, int32_t force, pic_tune_out *out);
 void pic_batch_destroy(pic_batch *batch);

@@ -26,6 +26,7 @@ struct pic_batch {
     int tile = 0;       // field-kernel tile shape shared by all members (pic_batch_tune)
     bool particles = false;
     bool use_graph = false;
+    bool stale = false;  // the device's blocks may not be those of `tile` (a tuner's failure left them so)
     int graph_steps = 0;
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
@@ -266,6 +267,7 @@ pic_status pic_batch_step(pic_batch *b, int64_t nsteps)
     if (nsteps < 0) return bfail(b, PIC_EINVAL, "nsteps must be >= 0");
     for (pic_ctx *c : b->ctx)
         if (c->poisoned) return bfail(b, PIC_ESTATE, "a member context is poisoned");
+    if (b->stale) return bfail(b, PIC_ESTATE, "a failed tuning left the batch without its launch tables");
     // order the batch's stream after, and the members' stream behind, this work
     BHIP(b, hipEventRecord(b->ev_in, b->ext));
     BHIP(b, hipStreamWaitEvent(b->stream, b->ev_in, 0));
@@ -313,9 +315,20 @@ pic_status pic_batch_tune(pic_batch *b, int32_t reps, int32_t force, pic_tune_ou
     pic_tune_out res{};
     res.nshapes = pic::N_TILE_SHAPES;
     int best = force;
+    const int before = b->tile;
+    // After a failure: the blocks and the table of the shape before, which a captured
+    // graph's launches were sized for (another shape's divisors would take their
+    // threads out of the grid), with the clock running again.
+    auto restore = [&](pic_status st) {
+        const std::string why = b->err;
+        b->stale = batch_upload_fields(b, before) != PIC_OK;
+        b->err = why;
+        return st;
+    };
+    // (launches still running read the tables written below)
+    BHIP(b, hipStreamSynchronize(b->ext));
+    BHIP(b, hipStreamSynchronize(b->stream));
     if (force < 0) {
-        BHIP(b, hipStreamSynchronize(b->ext));
-        BHIP(b, hipStreamSynchronize(b->stream));
         // save every member's field state; the timed launches advance it
         std::vector<void *> saved;
         std::vector<Mirror> mir(b->ctx.size());
@@ -353,17 +366,19 @@ pic_status pic_batch_tune(pic_batch *b, int32_t reps, int32_t force, pic_tune_ou
         }
         if (e0) (void)hipEventDestroy(e0);
         if (e1) (void)hipEventDestroy(e1);
+        (void)hipStreamSynchronize(b->stream);
         for (size_t q = 0; q < saved.size(); ++q) {
             if (ckpt_load(b->ctx[q], (char *)saved[q], mir[q]) != PIC_OK && st == PIC_OK)
                 st = bfail(b, PIC_EDEVICE, "restoring member %zu failed", q);
         }
         (void)hipStreamSynchronize(b->ext);
         for (void *p : saved) (void)hipFree(p);
-        if (st != PIC_OK) return st;
+        if (st != PIC_OK) return restore(st);
         best = pick_shape(res.ms, pic::DEFAULT_TILE);
     }
     pic_status st = batch_upload_fields(b, best);
-    if (st != PIC_OK) return st;
+    if (st != PIC_OK) return restore(st);
+    b->stale = false;
     if (b->use_graph) {
         st = batch_capture(b);
         if (st != PIC_OK) return st;
