@@ -501,15 +501,54 @@ int launch_stats(const DiagArgs &a, const unsigned long long *pushes, int nslots
 
 // ---- probes ----
 
-// sin and cos of x: x less the nearest multiple n of pi/2 (pi/2 as a sum of two
-// doubles, each product exact in the fma), then the Taylor series on [-pi/4,
-// pi/4] (the first terms left out are below 1e-19).  The library function's
-// reduction for huge arguments would take the field kernel that carries the
-// probes to twice its registers.
+// The first 1216 bits of 2 / pi, after 64 zero bits.
+static __device__ const unsigned long long TWO_OVER_PI[20] = {
+    0ull,
+    0xa2f9836e4e441529ull, 0xfc2757d1f534ddc0ull, 0xdb6295993c439041ull, 0xfe5163abdebbc561ull,
+    0xb7246e3a424dd2e0ull, 0x06492eea09d1921cull, 0xfe1deb1cb129a73eull, 0xe88235f52ebb4484ull,
+    0xe99c7026b45f7e41ull, 0x3991d639835339f4ull, 0x9c845f8bbdf9283bull, 0x1ff897ffde05980full,
+    0xef2f118b5a0a6d1full, 0x6d367ecf27cb09b7ull, 0x4f463f669e5fea2dull, 0x7527bac7ebe5f17bull,
+    0x3d0739f78a5292eaull, 0x6bfb5fb11f8d5d08ull, 0x56033046fc7b6babull};
+
+// |x| = m 2^e >= 2^45 less the nearest multiple of pi/2, and that multiple mod 4 (M.
+// Payne and R. Hanek, Radian reduction for trigonometric functions, 1983): the bits
+// of 2/pi above weight 2^(1-e) add multiples of 4 to 2/pi |x|, those more than 192
+// bits further down less than 2^-137, so m times the 192 bits between, mod 2^192, has
+// the multiple in its top 2 bits and the fraction below.
+__device__ __forceinline__ double reduce_large(double x, int &q)
+{
+    const unsigned long long bits = (unsigned long long)__double_as_longlong(x);
+    const int e = (int)((bits >> 52) & 2047) - 1075;
+    const unsigned long long m = (bits & ((1ull << 52) - 1)) | (1ull << 52);
+    const int b = e + 62, w = min(b >> 6, 16), sh = b & 63;
+    unsigned long long v[3];
+    for (int k = 0; k < 3; ++k) {
+        const unsigned long long hi = TWO_OVER_PI[w + k], lo = TWO_OVER_PI[w + k + 1];
+        v[k] = sh ? hi << sh | lo >> (64 - sh) : hi;
+    }
+    const unsigned long long p0 = m * v[2], c0 = __umul64hi(m, v[2]);
+    const unsigned long long p1 = m * v[1] + c0, c1 = __umul64hi(m, v[1]) + (p1 < c0);
+    const unsigned long long p2 = m * v[0] + c1;
+    const long long hi = (long long)(p2 << 2 | p1 >> 62);
+    const unsigned long long lo = p1 << 2 | p0 >> 62;
+    const double r = 1.5707963267948965580 * ((double)hi * 0x1p-64 + (double)lo * 0x1p-128);
+    const int n = (int)(p2 >> 62) + (hi < 0 ? 1 : 0);
+    q = (x < 0.0 ? -n : n) & 3;
+    if (!(fabs(x) < INFINITY)) return x - x;
+    return x < 0.0 ? -r : r;
+}
+
+// sin and cos of x: x less the nearest multiple n of pi/2, then the Taylor series on
+// [-pi/4, pi/4] (the first terms left out are below 1e-19).  Up to 2^45 pi/2 is a sum
+// of two doubles, each product exact in the fma (n times what they leave out of pi/2
+// is below 4e-20).  The library function's code would take the field kernel that
+// carries the probes to twice its registers.
 __device__ __forceinline__ void sincos_phase(double x, double &sn, double &cs)
 {
     const double n = rint(x * 0.63661977236758134308);
-    const double r = fma(-n, 6.123233995736766036e-17, fma(-n, 1.5707963267948965580, x));
+    double r = fma(-n, 6.123233995736766036e-17, fma(-n, 1.5707963267948965580, x));
+    int q = (int)(n - 4.0 * floor(0.25 * n));
+    if (!(fabs(x) < 0x1p45)) r = reduce_large(x, q);
     const double z = r * r;
     double s = -1.0 / 121645100408832000.0, c = -1.0 / 6402373705728000.0;  // -1/19!, -1/18!
     s = fma(s, z, 1.0 / 355687428096000.0);
@@ -530,7 +569,6 @@ __device__ __forceinline__ void sincos_phase(double x, double &sn, double &cs)
     c = fma(c, z, -0.5);
     s = fma(r * z, s, r);
     c = fma(z, c, 1.0);
-    const int q = (int)(n - 4.0 * floor(0.25 * n));
     const double a = q & 1 ? c : s, b = q & 1 ? s : c;
     sn = q & 2 ? -a : a;
     cs = q == 1 || q == 2 ? -b : b;
