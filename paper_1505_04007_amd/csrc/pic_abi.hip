@@ -415,25 +415,35 @@ pic::DiagArgs diag_args(pic_ctx *c)
 
 }  // namespace pich
 
-// n elements at src on the device, handed to use(elements, offset, number) through
-// pinned staging: a copy to pageable memory of 400 KB took 163 us, pinned 15.
+// n elements at src on the device (the stream has been waited for), handed to
+// use(elements, offset, number).  Through pinned staging where it pays: a copy to
+// pageable memory of 400 KB took 163 us, pinned 15, but making and freeing the staging
+// takes 50, and up to 256 KB a copy gains 2 to 9 of them.  So small arrays start it
+// only when a context reads them again and again (32x32x32 cells, E read once and
+// closed: pinned 170 us, pageable 120; read again 72, 76).
 constexpr size_t kPinBytes = 4u << 20;
+constexpr size_t kPinFrom = 1u << 18;
+constexpr int kPinReads = 8;
 
 template <class T, class Use>
 static pic_status read_back(pic_ctx *c, const T *src, size_t n, Use use)
 {
-    if (!c->pin && hipHostMalloc(&c->pin, kPinBytes, hipHostMallocDefault) != hipSuccess) {
+    if (!c->pin && (n * sizeof(T) > kPinFrom || ++c->small_reads > kPinReads) &&
+        hipHostMalloc(&c->pin, kPinBytes, hipHostMallocDefault) != hipSuccess) {
         (void)hipGetLastError();
         c->pin = nullptr;
     }
-    std::vector<T> pageable;  // where there is no pinned memory to be had
     const size_t chunk = kPinBytes / sizeof(T);
-    if (!c->pin) pageable.resize(std::min(n, chunk));
+    std::vector<T> pageable(c->pin ? 0 : std::min(n, chunk));
     T *buf = c->pin ? (T *)c->pin : pageable.data();
     for (size_t off = 0; off < n; off += chunk) {
         const size_t m = std::min(chunk, n - off);
-        HIP_TRY(c, hipMemcpyAsync(buf, src + off, m * sizeof(T), hipMemcpyDeviceToHost, c->stream));
-        HIP_TRY(c, hipStreamSynchronize(c->stream));
+        if (c->pin) {
+            HIP_TRY(c, hipMemcpyAsync(buf, src + off, m * sizeof(T), hipMemcpyDeviceToHost, c->stream));
+            HIP_TRY(c, hipStreamSynchronize(c->stream));
+        } else {
+            HIP_TRY(c, hipMemcpy(buf, src + off, m * sizeof(T), hipMemcpyDeviceToHost));
+        }
         use(buf, off, m);
     }
     return PIC_OK;

@@ -88,7 +88,8 @@ struct pic_ctx {
     bool timed_now = false;  // the launch being issued has a start event
 
     long long step = 0;
-    void *pin = nullptr;     // pinned staging of the read-backs (kPinBytes), made by the first
+    void *pin = nullptr;     // pinned staging of the read-backs (kPinBytes), made when one pays for it
+    int small_reads = 0;     // arrays read back without it
     bool probe_due = false;  // the last step's probes wait for the next H update (or the call's end)
     int tile = 0;  // field-kernel tile shape (pic_tune)
     int sort_every = 0, check_every = 0;
