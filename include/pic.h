@@ -381,8 +381,11 @@ void pic_destroy(pic_ctx *ctx);
  *   and replays it whenever all members are at the start of a sort period;
  *   other steps are issued directly.
  * pic_batch_step: advance every member by nsteps steps.  Each member's
- *   results equal those of pic_step on that member alone (same kernels, same
- *   per-cell arithmetic).  No non-finite poll is made; use pic_diag.
+ *   results equal those of pic_step on that member alone: the fields of given
+ *   currents and a particle's kick and move in given fields bit for bit (the
+ *   same arithmetic per cell and per particle); the FP32 sums of the bunch
+ *   current over particles have no fixed order in either.  No non-finite
+ *   poll is made; use pic_diag.
  * Errors: PIC_EINVAL (arguments), PIC_ESTATE (a poisoned member),
  *   PIC_EDEVICE, PIC_ENOMEM; the message is in pic_batch_last_error.
  */

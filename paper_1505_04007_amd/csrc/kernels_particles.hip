@@ -109,7 +109,9 @@ __device__ __forceinline__ float2 ld2(const float *p)
 }
 
 // Trilinear value of a component that sits at half nodes along the axes
-// flagged (HX, HY, HZ).
+// flagged (HX, HY, HZ).  The fused operations are written out, in the gathers and
+// where the split push puts a value together (quad_pair, quad_scalar), so that every
+// kernel rounds alike: a particle's kick does not depend on which one pushes it.
 template <int HX, int HY, int HZ>
 __device__ __forceinline__ float gather_pair(const float *__restrict__ f, const XPair &X,
                                              const Axis2 &Y, const Axis2 &Z)
@@ -122,7 +124,7 @@ __device__ __forceinline__ float gather_pair(const float *__restrict__ f, const 
             const int o = X.o[HX] + (b ? Y.o1[HY] : Y.o0[HY]) + (c ? Z.o1[HZ] : Z.o0[HZ]);
             const float w = (b ? Y.m1[HY] : Y.m0[HY]) * (c ? Z.m1[HZ] : Z.m0[HZ]);
             const float2 p = ld2(f + o);
-            v += w * (X.wa[HX] * p.x + X.wb[HX] * p.y);
+            v = fmaf(w, fmaf(X.wa[HX], p.x, X.wb[HX] * p.y), v);
         }
     return v;
 }
@@ -142,7 +144,7 @@ __device__ __forceinline__ float gather_scalar(const float *__restrict__ f, cons
                               (c ? Z.o1[HZ] : Z.o0[HZ]);
                 const float w = (q ? X.m1[HX] : X.m0[HX]) * (b ? Y.m1[HY] : Y.m0[HY]) *
                                 (c ? Z.m1[HZ] : Z.m0[HZ]);
-                v += w * G(f)[o];
+                v = fmaf(w, G(f)[o], v);
             }
     return v;
 }
@@ -773,47 +775,72 @@ constexpr int SPLIT_MAX = 1 << 16;
 // 11.3, 9.8, 8.6 us; 1000: 9.5, 9.0, 8.4, 7.8).
 constexpr int SPLIT_LANES = 16;
 
-// The sum over the 4 lanes l, l ^ 16, l ^ 32, l ^ 48, the same in each of them.
-__device__ __forceinline__ float quad_sum(float v)
+// v of the lanes of corner 0..3 of this lane's particle (lanes l, l ^ 16, l ^ 32, l ^ 48).
+struct Quad {
+    float v[4];
+};
+__device__ __forceinline__ Quad quad_all(float v)
 {
     const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-    v = __uint_as_float(r[0]) + __uint_as_float(r[1]);
-    const auto t = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-    return __uint_as_float(t[0]) + __uint_as_float(t[1]);
+    const auto e = __builtin_amdgcn_permlane32_swap(r[0], r[0], false, false);
+    const auto o = __builtin_amdgcn_permlane32_swap(r[1], r[1], false, false);
+    return {{__uint_as_float(e[0]), __uint_as_float(o[0]), __uint_as_float(e[1]), __uint_as_float(o[1])}};
 }
 
-// One (y, z) corner of the gather, by node and half node: offset and weight.
+// Offsets of the (y, z) corner that a lane loads, by node and half node.
 struct Corner {
-    int o[2];
-    float m[2];
+    int y[2], z[2];
 };
 
-__device__ __forceinline__ Corner corner(const Axis2 &A, int c)
+__device__ __forceinline__ Corner corner(const Axis2 &Y, const Axis2 &Z, int c)
 {
     Corner r;
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
-        r.o[h] = c ? A.o1[h] : A.o0[h];
-        r.m[h] = c ? A.m1[h] : A.m0[h];
+        // sums, as a choice of two members would put them in scratch
+        r.y[h] = Y.o0[h] + (c & 1) * (Y.o1[h] - Y.o0[h]);
+        r.z[h] = Z.o0[h] + (c >> 1) * (Z.o1[h] - Z.o0[h]);
     }
     return r;
 }
 
+// gather_pair and gather_scalar with a corner's loads in each of 4 lanes.
 template <int HX, int HY, int HZ>
-__device__ __forceinline__ float corner_pair(const float *__restrict__ f, const XPair &X, const Corner &Y,
-                                             const Corner &Z)
+__device__ __forceinline__ float quad_pair(float2 p, const XPair &X, const Axis2 &Y, const Axis2 &Z)
 {
-    const float2 p = ld2(f + (X.o[HX] + Y.o[HY] + Z.o[HZ]));
-    return Y.m[HY] * Z.m[HZ] * (X.wa[HX] * p.x + X.wb[HX] * p.y);
+    const Quad t = quad_all(fmaf(X.wa[HX], p.x, X.wb[HX] * p.y));
+    float v = 0.f;
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+        v = fmaf((c & 1 ? Y.m1[HY] : Y.m0[HY]) * (c & 2 ? Z.m1[HZ] : Z.m0[HZ]), t.v[c], v);
+    return v;
 }
 
 template <int HX, int HY, int HZ>
-__device__ __forceinline__ float corner_scalar(const float *__restrict__ f, const Axis2 &X, const Corner &Y,
-                                               const Corner &Z)
+__device__ __forceinline__ float quad_scalar(float2 p, const Axis2 &X, const Axis2 &Y, const Axis2 &Z)
 {
-    const int o = Y.o[HY] + Z.o[HZ];
-    const float p = G(f)[X.o0[HX] + o], q = G(f)[X.o1[HX] + o];
-    return Y.m[HY] * Z.m[HZ] * (X.m0[HX] * p + X.m1[HX] * q);
+    const Quad a = quad_all(p.x), b = quad_all(p.y);
+    float v = 0.f;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        const float my = c & 1 ? Y.m1[HY] : Y.m0[HY], mz = c & 2 ? Z.m1[HZ] : Z.m0[HZ];
+        v = fmaf(X.m0[HX] * my * mz, a.v[c], v);
+        v = fmaf(X.m1[HX] * my * mz, b.v[c], v);
+    }
+    return v;
+}
+
+template <int HX, int HY, int HZ>
+__device__ __forceinline__ float2 corner_pair(const float *__restrict__ f, const XPair &X, const Corner &C)
+{
+    return ld2(f + (X.o[HX] + C.y[HY] + C.z[HZ]));
+}
+
+template <int HX, int HY, int HZ>
+__device__ __forceinline__ float2 corner_scalar(const float *__restrict__ f, const Axis2 &X, const Corner &C)
+{
+    const int o = C.y[HY] + C.z[HZ];
+    return make_float2(G(f)[X.o0[HX] + o], G(f)[X.o1[HX] + o]);
 }
 
 template <int PX>
@@ -839,28 +866,35 @@ __global__ __launch_bounds__(256) void k_push_split(PartArgs a)
         Axis2 AY, AZ;
         axis_corners(yg, a.ny, a.per[1], a.nx, AY);
         axis_corners(zg, a.nz, a.per[2], a.nx * a.ny, AZ);
-        const Corner CY = corner(AY, c & 1), CZ = corner(AZ, c >> 1);
+        const Corner C = corner(AY, AZ, c);
         float e0, e1, e2, h0, h1, h2;
+        // every load before any exchange
         if (PX) {
             Axis2 AX;
             axis_corners(xg, a.nx, a.per[0], 1, AX);
-            e0 = corner_scalar<1, 0, 0>(a.E[0], AX, CY, CZ);
-            e1 = corner_scalar<0, 1, 0>(a.E[1], AX, CY, CZ);
-            e2 = corner_scalar<0, 0, 1>(a.E[2], AX, CY, CZ);
-            h0 = corner_scalar<0, 1, 1>(a.B[0], AX, CY, CZ);
-            h1 = corner_scalar<1, 0, 1>(a.B[1], AX, CY, CZ);
-            h2 = corner_scalar<1, 1, 0>(a.B[2], AX, CY, CZ);
+            const float2 q0 = corner_scalar<1, 0, 0>(a.E[0], AX, C), q1 = corner_scalar<0, 1, 0>(a.E[1], AX, C);
+            const float2 q2 = corner_scalar<0, 0, 1>(a.E[2], AX, C), q3 = corner_scalar<0, 1, 1>(a.B[0], AX, C);
+            const float2 q4 = corner_scalar<1, 0, 1>(a.B[1], AX, C), q5 = corner_scalar<1, 1, 0>(a.B[2], AX, C);
+            e0 = quad_scalar<1, 0, 0>(q0, AX, AY, AZ);
+            e1 = quad_scalar<0, 1, 0>(q1, AX, AY, AZ);
+            e2 = quad_scalar<0, 0, 1>(q2, AX, AY, AZ);
+            h0 = quad_scalar<0, 1, 1>(q3, AX, AY, AZ);
+            h1 = quad_scalar<1, 0, 1>(q4, AX, AY, AZ);
+            h2 = quad_scalar<1, 1, 0>(q5, AX, AY, AZ);
         } else {
             XPair XP;
             x_pairs(xg, a.nx, XP);
-            e0 = corner_pair<1, 0, 0>(a.E[0], XP, CY, CZ);
-            e1 = corner_pair<0, 1, 0>(a.E[1], XP, CY, CZ);
-            e2 = corner_pair<0, 0, 1>(a.E[2], XP, CY, CZ);
-            h0 = corner_pair<0, 1, 1>(a.B[0], XP, CY, CZ);
-            h1 = corner_pair<1, 0, 1>(a.B[1], XP, CY, CZ);
-            h2 = corner_pair<1, 1, 0>(a.B[2], XP, CY, CZ);
+            const float2 q0 = corner_pair<1, 0, 0>(a.E[0], XP, C), q1 = corner_pair<0, 1, 0>(a.E[1], XP, C);
+            const float2 q2 = corner_pair<0, 0, 1>(a.E[2], XP, C), q3 = corner_pair<0, 1, 1>(a.B[0], XP, C);
+            const float2 q4 = corner_pair<1, 0, 1>(a.B[1], XP, C), q5 = corner_pair<1, 1, 0>(a.B[2], XP, C);
+            e0 = quad_pair<1, 0, 0>(q0, XP, AY, AZ);
+            e1 = quad_pair<0, 1, 0>(q1, XP, AY, AZ);
+            e2 = quad_pair<0, 0, 1>(q2, XP, AY, AZ);
+            h0 = quad_pair<0, 1, 1>(q3, XP, AY, AZ);
+            h1 = quad_pair<1, 0, 1>(q4, XP, AY, AZ);
+            h2 = quad_pair<1, 1, 0>(q5, XP, AY, AZ);
         }
-        boris(a.ah, quad_sum(e0), quad_sum(e1), quad_sum(e2), quad_sum(h0), quad_sum(h1), quad_sum(h2), u0, u1, u2);
+        boris(a.ah, e0, e1, e2, h0, h1, h2, u0, u1, u2);
     }
     const float g = rsqrtf(1.f + u0 * u0 + u1 * u1 + u2 * u2);
     const float nx1 = x + a.S * u0 * g, ny1 = y + a.S * u1 * g, nz1 = z + a.S * u2 * g;
