@@ -603,24 +603,39 @@ __device__ __forceinline__ void deposit_fixed(const PartArgs &a, FixLds &L, unsi
     }
 }
 
-// The passes of a wavefront's rows with at least ROW_LANES lanes; the lanes left over.
+// A row of which a wavefront holds half its lanes or more lies in the dense part of the
+// bunch, where most wavefronts add to the same few cache lines and per-lane atomics on
+// one address follow each other at 17 ns: there the rows beside it (the particles that
+// moved back over a cell's face) are passes from DENSE_LANES lanes on.  Particles moving
+// every way, without / with: 2e5 in 180 cells 358 / 146 us, 1e6 in 4000 cells 590 / 241,
+// 2e5 with 15 % transverse velocities 134 / 71 (from 3 lanes on 93, from 5 on 126); in
+// beams sorted by row there are none (film 1e6, grating 1e7, batch: within 0.4 %).
+constexpr int DENSE_LANES = 2;
+
+// The passes of a wavefront's rows; the lanes left over.
 __device__ __forceinline__ unsigned long long row_passes(const PartArgs &a, RowLds &L, unsigned long long rem,
                                                          int lane, const int base[3], float x0, float x1, bool yz)
 {
-    unsigned long long small = 0;
-    while (rem) {
-        const int leader = __ffsll((long long)rem) - 1;
-        // a lane behind the leader by less than a cell still joins its pass
-        const int X0 = __builtin_amdgcn_readlane(base[0], leader) - 1;
-        const int by = __builtin_amdgcn_readlane(base[1], leader);
-        const int bz = __builtin_amdgcn_readlane(base[2], leader);
-        const unsigned long long m =
-            __ballot(base[1] == by && base[2] == bz && (unsigned)(base[0] - X0) < (unsigned)ROW_BASES) & rem;
-        rem &= ~m;
-        if (__popcll(m) < ROW_LANES) small |= m;
-        else deposit_rows(a, L, m, lane, x0, x1, X0, by, bz, yz);
+    const int lanes = __popcll(rem);
+    for (int least = ROW_LANES;; least = DENSE_LANES) {
+        unsigned long long small = 0;
+        int most = 0;
+        while (rem) {
+            const int leader = __ffsll((long long)rem) - 1;
+            // a lane behind the leader by less than a cell still joins its pass
+            const int X0 = __builtin_amdgcn_readlane(base[0], leader) - 1;
+            const int by = __builtin_amdgcn_readlane(base[1], leader);
+            const int bz = __builtin_amdgcn_readlane(base[2], leader);
+            const unsigned long long m =
+                __ballot(base[1] == by && base[2] == bz && (unsigned)(base[0] - X0) < (unsigned)ROW_BASES) & rem;
+            rem &= ~m;
+            most = max(most, (int)__popcll(m));
+            if (__popcll(m) < least) small |= m;
+            else deposit_rows(a, L, m, lane, x0, x1, X0, by, bz, yz);
+        }
+        if (least != ROW_LANES || 2 * most < lanes || !small) return small;
+        rem = small;
     }
-    return small;
 }
 
 template <int MODE, int PX, int FIX>
@@ -774,6 +789,14 @@ constexpr int SPLIT_MAX = 1 << 16;
 // not depend on their number (2e4 particles, least number 4, 7, 10, 16: 13.4,
 // 11.3, 9.8, 8.6 us; 1000: 9.5, 9.0, 8.4, 7.8).
 constexpr int SPLIT_LANES = 16;
+// But in the dense part of a bunch of more than SPLIT_DENSE (as for DENSE_LANES above),
+// the particles that lie, in sorted order, between those of the widest row form passes
+// from SPLIT_DENSE_LANES on: they are of its cells, where a neighbouring row of a cold
+// beam lies before or after.  Particles moving every way, without / with: 6000 in one
+// cell 28.6 / 17.5 us, 2e4 in 180 cells 45 / 27, 65536 130 / 68; fewer than 4096 in one
+// cell lose as much to the passes' latency as they gain (2000: 14.3 / 14.8).
+constexpr int SPLIT_DENSE = 4096;
+constexpr int SPLIT_DENSE_LANES = 3;
 
 // v of the lanes of corner 0..3 of this lane's particle (lanes l, l ^ 16, l ^ 32, l ^ 48).
 struct Quad {
@@ -843,7 +866,8 @@ __device__ __forceinline__ float2 corner_scalar(const float *__restrict__ f, con
     return make_float2(G(f)[X.o0[HX] + o], G(f)[X.o1[HX] + o]);
 }
 
-template <int PX>
+// DENSE: more than SPLIT_DENSE particles.
+template <int PX, int DENSE>
 __global__ __launch_bounds__(256) void k_push_split(PartArgs a)
 {
     const int lane = threadIdx.x & 63, c = lane >> 4;
@@ -930,49 +954,58 @@ __global__ __launch_bounds__(256) void k_push_split(PartArgs a)
     unsigned long long rem = __ballot(b.w & 1), small = 0;
     const bool yz = __ballot(b.w & 2) != 0ull;
     if (threadIdx.x == 0 && rem) gatomic_add(G(a.pushes) + blk, (unsigned long long)__popcll(rem));
+    const int lanes = __popcll(rem);
+    unsigned long long widest = 0;
     int buf = 0;
-    while (rem) {
-        const int leader = __ffsll((long long)rem) - 1;
-        const int X0 = __builtin_amdgcn_readlane(b.x, leader) - 1;
-        const int by = __builtin_amdgcn_readlane(b.y, leader);
-        const int bz = __builtin_amdgcn_readlane(b.z, leader);
-        const unsigned long long m = __ballot(b.y == by && b.z == bz && (unsigned)(b.x - X0) < (unsigned)ROW_BASES) & rem;
-        rem &= ~m;
-        if (__popcll(m) < SPLIT_LANES) {
-            small |= m;
-            continue;
-        }
-        const unsigned own = (unsigned)(m >> (16 * wave)) & 0xffffu;
-        fvec4 jx = {0.f, 0.f, 0.f, 0.f}, jyz = {0.f, 0.f, 0.f, 0.f};
-        if (own) row_chunk<true>(L, 16 * wave, own, lane, X0, yz, jx, jyz);
-        int waves = 0;
+    for (int least = SPLIT_LANES;; least = SPLIT_DENSE_LANES) {
+        while (rem) {
+            const int leader = __ffsll((long long)rem) - 1;
+            const int X0 = __builtin_amdgcn_readlane(b.x, leader) - 1;
+            const int by = __builtin_amdgcn_readlane(b.y, leader);
+            const int bz = __builtin_amdgcn_readlane(b.z, leader);
+            const unsigned long long m =
+                __ballot(b.y == by && b.z == bz && (unsigned)(b.x - X0) < (unsigned)ROW_BASES) & rem;
+            rem &= ~m;
+            if (__popcll(m) < least) {
+                small |= m;
+                continue;
+            }
+            if (DENSE && __popcll(m) > __popcll(widest)) widest = m;
+            const unsigned own = (unsigned)(m >> (16 * wave)) & 0xffffu;
+            fvec4 jx = {0.f, 0.f, 0.f, 0.f}, jyz = {0.f, 0.f, 0.f, 0.f};
+            if (own) row_chunk<true>(L, 16 * wave, own, lane, X0, yz, jx, jyz);
+            int waves = 0;
 #pragma unroll
-        for (int w = 0; w < 4; ++w) waves += ((m >> (16 * w)) & 0xffffull) != 0;
-        if (waves < 3) {
+            for (int w = 0; w < 4; ++w) waves += ((m >> (16 * w)) & 0xffffull) != 0;
+            if (waves < 3) {
+                if (own) {
+                    const RowOut r = row_out(a, lane, X0, by, bz);
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) row_add(a, r, lane, j, yz, jx[j], jyz[j]);
+                }
+                continue;
+            }
             if (own) {
-                const RowOut r = row_out(a, lane, X0, by, bz);
 #pragma unroll
-                for (int j = 0; j < 4; ++j) row_add(a, r, lane, j, yz, jx[j], jyz[j]);
+                for (int j = 0; j < 4; ++j) {
+                    R[buf][wave][j][lane] = jx[j];
+                    R[buf][wave][4 + j][lane] = jyz[j];
+                }
             }
-            continue;
+            __syncthreads();
+            float sx = 0.f, syz = 0.f;
+#pragma unroll
+            for (int w = 0; w < 4; ++w)
+                if ((m >> (16 * w)) & 0xffffull) {
+                    sx += R[buf][w][wave][lane];
+                    syz += R[buf][w][4 + wave][lane];
+                }
+            row_add(a, row_out(a, lane, X0, by, bz), lane, wave, yz, sx, syz);
+            buf ^= 1;
         }
-        if (own) {
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                R[buf][wave][j][lane] = jx[j];
-                R[buf][wave][4 + j][lane] = jyz[j];
-            }
-        }
-        __syncthreads();
-        float sx = 0.f, syz = 0.f;
-#pragma unroll
-        for (int w = 0; w < 4; ++w)
-            if ((m >> (16 * w)) & 0xffffull) {
-                sx += R[buf][w][wave][lane];
-                syz += R[buf][w][4 + wave][lane];
-            }
-        row_add(a, row_out(a, lane, X0, by, bz), lane, wave, yz, sx, syz);
-        buf ^= 1;
+        if (!DENSE || least != SPLIT_LANES || !widest || 2 * __popcll(widest) < lanes) break;
+        rem = small & (~0ull >> __clzll((long long)widest)) & (~0ull << (__ffsll((long long)widest) - 1));
+        small &= ~rem;
     }
     if ((small >> slot) & 1ull) quarter_deposit(a, c, base, x0, y0, z0, x1, y1, z1);
 }
@@ -1000,8 +1033,11 @@ void launch_push_deposit(const PartArgs &a, int mode, hipStream_t s)
     // mode 2: wavefront-reduced deposit into the fixed-point current
     const bool fix = mode == 2 && a.Jq[0];
     if (mode == 0 && a.n <= SPLIT_MAX) {
-        if (a.per[0]) hipLaunchKernelGGL((k_push_split<1>), dim3(nb), dim3(256), 0, s, a);
-        else hipLaunchKernelGGL((k_push_split<0>), dim3(nb), dim3(256), 0, s, a);
+        const bool dense = a.n > SPLIT_DENSE;
+        if (a.per[0] && dense) hipLaunchKernelGGL((k_push_split<1, 1>), dim3(nb), dim3(256), 0, s, a);
+        else if (a.per[0]) hipLaunchKernelGGL((k_push_split<1, 0>), dim3(nb), dim3(256), 0, s, a);
+        else if (dense) hipLaunchKernelGGL((k_push_split<0, 1>), dim3(nb), dim3(256), 0, s, a);
+        else hipLaunchKernelGGL((k_push_split<0, 0>), dim3(nb), dim3(256), 0, s, a);
         return;
     }
     if (a.per[0]) {
