@@ -191,29 +191,30 @@ __device__ __forceinline__ SlotF slot_factors(float x0, float x1, int n)
     return {0.5f * (s0 + s1), RSQRT12 * (s1 - s0), clamp01(1.f - e1) - clamp01(1.f - e0)};
 }
 
-// Slot s (0..53) of the deposit window: component and offsets from the base node.
-//   Jx: s = a*9 + b*3 + c        (edge a in 0..1, nodes b, c in 0..2)
-//   Jy: s = 18 + a*6 + m*3 + c   (node a, edge m, node c)
-//   Jz: s = 36 + a*6 + b*2 + m   (nodes a, b, edge m)
+// Slot s (0..53) of the deposit window: component and offsets from the base node, the
+// 2 edges or 3 nodes along x of a grid row side by side.
+//   Jx: s = 6 b + 2 c + a         (edge a in 0..1, nodes b, c in 0..2)
+//   Jy: s = 18 + 9 m + 3 c + a    (node a, edge m, node c)
+//   Jz: s = 36 + 6 b + 3 m + a    (nodes a, b, edge m)
 __device__ __forceinline__ void slot_geom(int s, int &comp, int &oi, int &oj, int &ok)
 {
     if (s < 18) {
         comp = 0;
-        oi = s / 9;
-        oj = (s / 3) % 3;
-        ok = s % 3;
+        oi = s % 2;
+        oj = s / 6;
+        ok = (s / 2) % 3;
     } else if (s < 36) {
         const int t = s - 18;
         comp = 1;
-        oi = t / 6;
-        oj = (t / 3) % 2;
-        ok = t % 3;
+        oi = t % 3;
+        oj = t / 9;
+        ok = (t / 3) % 3;
     } else {
         const int t = s - 36;
         comp = 2;
-        oi = t / 6;
-        oj = (t / 2) % 3;
-        ok = t % 2;
+        oi = t % 3;
+        oj = t / 6;
+        ok = (t / 3) % 2;
     }
 }
 
@@ -519,6 +520,14 @@ __device__ __forceinline__ bool leaves(const PartArgs &a, float x, float y, floa
 // instructions each, and their short ones with 54 atomics per lane, took 30.1 us for
 // 2e5 particles in 96x64x96 cells, now 24.2 (2e4: 20.3 -> 19.5, 1e6: 59.1 -> 57.1);
 // what is left is the 54 units of every particle and the gather.
+//
+// A wavefront whose windows do not fit one such product, with less than 8 lanes in any,
+// has them added lane by lane, in bunches of up to FIX_LANE_MAX, where the time is the
+// slowest wavefront's: 200 particles in 4000 cells 22.7 -> 10.2 us (15.0 in the sums
+// over lanes), 2000 21.4 -> 12.1 (15.8), 2e4 in 5e5 cells 29.3 -> 21.0.  Of more, the
+// products keep the chip busier: 1e5 in 5e5 cells 51 us, lane by lane 57.
+constexpr int FIX_WINDOWS = 16;
+constexpr int FIX_LANE_MAX = 1 << 16;
 typedef int ivec4 __attribute__((ext_vector_type(4)));
 struct FixLds {
     alignas(16) int units[16][68];  // by slot (rows that 16 lanes read at once start 4 banks apart), by particle
@@ -534,9 +543,24 @@ __device__ __forceinline__ ivec4 byte_planes(ivec4 v)
                  (int)__builtin_amdgcn_perm(hi23, hi01, 0x05040100), (int)__builtin_amdgcn_perm(hi23, hi01, 0x07060302)};
 }
 
+// Whether the lanes of rem have more than FIX_WINDOWS windows, none of 8 lanes or more
+// among the first of them.
+__device__ __forceinline__ bool scattered(unsigned long long rem, int key)
+{
+    int windows = 0;
+    while (rem) {
+        const int leader = __ffsll((long long)rem) - 1;
+        const unsigned long long m = __ballot(key == __builtin_amdgcn_readlane(key, leader)) & rem;
+        rem &= ~m;
+        if (__popcll(m) >= 8) return false;
+        if (++windows > FIX_WINDOWS) return true;
+    }
+    return false;
+}
+
 template <class Units>
 __device__ __forceinline__ void deposit_fixed(const PartArgs &a, FixLds &L, unsigned long long rem, int lane,
-                                              const int base[3], Units units)
+                                              const int base[3], int key, Units units)
 {
     const int n = lane & 15, q = lane >> 4;
 #pragma unroll
@@ -556,19 +580,21 @@ __device__ __forceinline__ void deposit_fixed(const PartArgs &a, FixLds &L, unsi
 #pragma unroll
         for (int b = 0; b < 4; ++b) B[T][b] = ivec4{p[0][b], p[1][b], p[2][b], p[3][b]};
     }
-    const int key = (base[0] + 1) + (a.nx + 2) * ((base[1] + 1) + (a.ny + 2) * (base[2] + 1));
     // the window's first cell where the window is inside the grid, else -1
     const bool in = base[0] >= 0 && base[0] + 2 < a.nx && base[1] >= 0 && base[1] + 2 < a.ny && base[2] >= 0 &&
                     base[2] + 2 < a.nz;
     const int first = in ? base[0] + a.nx * (base[1] + a.ny * base[2]) : -1;
     int rel[4];
     unsigned long long *J[4];
+    // (held in registers: a choice of the argument block's members would go through scratch)
+    unsigned long long *J0 = a.Jq[0], *J1 = a.Jq[1], *J2 = a.Jq[2];
+    asm("" : "+s"(J0), "+s"(J1), "+s"(J2));
 #pragma unroll
     for (int T = 0; T < 4; ++T) {
         int comp, oi, oj, ok;
         slot_geom(min(16 * T + n, 53), comp, oi, oj, ok);
         rel[T] = oi + a.nx * (oj + a.ny * ok);
-        J[T] = comp == 0 ? a.Jq[0] : (comp == 1 ? a.Jq[1] : a.Jq[2]);
+        J[T] = comp == 0 ? J0 : (comp == 1 ? J1 : J2);
     }
     while (rem) {
         // up to 16 windows: w in row 4 (w % 4) + w / 4, so that few of them lie in
@@ -613,7 +639,7 @@ __device__ __forceinline__ void deposit_fixed(const PartArgs &a, FixLds &L, unsi
                     const int p = lead[j];
                     int comp;
                     const int cell = slot_index(a, s, L.base[0][p], L.base[1][p], L.base[2][p], comp);
-                    if (cell >= 0) add_fixed(a, comp, cell, tot);
+                    if (cell >= 0) gatomic_add(G(J[T]) + cell, (unsigned long long)(long long)tot);
                 }
             }
         }
@@ -752,8 +778,14 @@ __device__ __forceinline__ void push_body(const PartArgs &a, int blk)
         __shared__ FixLds L;
         const AxisF fx = axis_factors(x0, x1, base[0]), fy = axis_factors(y0, y1, base[1]),
                     fz = axis_factors(z0, z1, base[2]);
-        deposit_fixed(a, L, rem, lane, base,
-                      [&](int s) { return __float2int_rn(a.qd * slot_value(fx, fy, fz, s) * a.qscale); });
+        const auto units = [&](float c) { return __float2int_rn(a.qd * c * a.qscale); };
+        const int key = (base[0] + 1) + (a.nx + 2) * ((base[1] + 1) + (a.ny + 2) * (base[2] + 1));
+        if (a.n <= FIX_LANE_MAX && scattered(rem, key)) {
+            if (dep)
+                lane_deposit(a, base, fx, fy, fz, units, [&](int comp, int q, int u) { add_fixed(a, comp, q, u); });
+        } else {
+            deposit_fixed(a, L, rem, lane, base, key, [&](int s) { return units(slot_value(fx, fy, fz, s)); });
+        }
         return;
     }
     if (MODE == 0) {
