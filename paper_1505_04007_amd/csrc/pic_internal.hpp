@@ -548,7 +548,7 @@ __device__ __forceinline__ void sincos_phase(double x, double &sn, double &cs)
     const double n = rint(x * 0.63661977236758134308);
     double r = fma(-n, 6.123233995736766036e-17, fma(-n, 1.5707963267948965580, x));
     int q = (int)(n - 4.0 * floor(0.25 * n));
-    if (!(fabs(x) < 0x1p45)) r = reduce_large(x, q);
+    if (__builtin_expect(!(fabs(x) < 0x1p45), 0)) r = reduce_large(x, q);
     const double z = r * r;
     double s = -1.0 / 121645100408832000.0, c = -1.0 / 6402373705728000.0;  // -1/19!, -1/18!
     s = fma(s, z, 1.0 / 355687428096000.0);
