@@ -125,6 +125,25 @@ def traffic_for(fam, wname):
     return counters_for(fam, wname).get("bytes_per_launch")
 
 
+def roofline(kernel, avg_s, algo, rec):
+    """The kernel's rate against the limit it is nearer to: HBM bandwidth, by its
+    algorithmic bytes, or VALU issue, by the committed instruction count per launch over
+    the live launch time where there is one.  The other stands beside it."""
+    hbm = {"achieved": round(algo / avg_s / 1e9, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
+           "frac": round(algo / avg_s / 1e9 / HBM_PEAK_GBS, 4)}
+    parts = {"hbm": hbm}
+    if rec.get("valu_per_launch"):
+        va = rec["valu_per_launch"] / avg_s / 1e9
+        parts["alu"] = {"achieved": round(va, 1), "peak": VALU_PEAK_G, "unit": "G wave64-VALU-instructions/s",
+                        "frac": round(va / VALU_PEAK_G, 4)}
+    bound = max(parts, key=lambda k: parts[k]["frac"])
+    roof = {"bound": bound, **parts.pop(bound), "traffic": rec.get("bytes_per_launch"), "kernel": kernel,
+            "algorithmic_bytes_per_launch": algo, "avg_launch_ms": round(avg_s * 1e3, 4), **parts}
+    if rec.get("valu_per_launch"):
+        roof["valu_per_launch"] = rec["valu_per_launch"]
+    return roof
+
+
 def cpu_baseline(w, steps=6):
     """The FP64 oracle on the whole workload (full grid, every particle) for
     `steps` steps after one untimed step, its field loops and its particle
@@ -418,22 +437,7 @@ def main():
     avg_s = ms_tot / 1e3 / max(launches, 1)
     per_step_push = pushes / args.steps
     algo = algorithmic_bytes(w, dom, per_step_push, st["pbox"])
-    roof = None
-    if algo is not None and avg_s > 0:
-        ach = algo / avg_s / 1e9
-        rec = counters_for(dom, w.name)
-        hbm = {"bound": "hbm", "achieved": round(ach, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
-               "frac": round(ach / HBM_PEAK_GBS, 4), "traffic": rec.get("bytes_per_launch")}
-        roof = dict(hbm, kernel=dom, algorithmic_bytes_per_launch=algo, avg_launch_ms=round(avg_s * 1e3, 4))
-        if rec.get("valu_per_launch"):
-            # VALU-issue bound: committed SQ_INSTS_VALU per launch over the live launch time
-            va = rec["valu_per_launch"] / avg_s / 1e9
-            roof = {"bound": "alu", "achieved": round(va, 1), "peak": VALU_PEAK_G,
-                    "unit": "G wave64-VALU-instructions/s", "frac": round(va / VALU_PEAK_G, 4),
-                    "traffic": rec.get("bytes_per_launch"), "kernel": dom,
-                    "valu_per_launch": rec["valu_per_launch"], "avg_launch_ms": round(avg_s * 1e3, 4),
-                    "hbm": {k: hbm[k] for k in ("achieved", "peak", "unit", "frac")},
-                    "algorithmic_bytes_per_launch": algo}
+    roof = roofline(dom, avg_s, algo, counters_for(dom, w.name)) if algo is not None and avg_s > 0 else None
     kernels = {}
     for f in FAMILIES:
         ms, n = fams[f]
