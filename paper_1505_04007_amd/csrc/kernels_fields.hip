@@ -3,18 +3,20 @@
 //
 // One thread per cell, one workgroup per run of 256 cells in memory order (the
 // autotuner may pick another shape, as (x, y) tiles of one z plane, from a fixed
-// table), x fastest so a wavefront reads contiguous rows.  Each cell reads its own three old values and the three neighbour values its
-// curl needs (+x/+y/+z for H, -x/-y/-z for E); the neighbours are the own
-// values of adjacent lanes, rows and planes and are served by L1/L2, so the
-// HBM traffic stays close to one read and one write of every array.
+// table), x fastest so a wavefront reads contiguous rows.  Each cell reads its own
+// three old values and the three neighbour values its curl needs (+x/+y/+z for H,
+// -x/-y/-z for E); the neighbours are the own values of adjacent lanes, rows and
+// planes and are served by L1/L2, so the HBM traffic stays close to one read and
+// one write of every array.
 // Neighbour loads are branch-free (index clamped to the cell itself, value
 // selected to 0 or wrapped) so every load of a thread issues back to back.
 // Measured on MI355X this barrier-free form streams faster than an
 // LDS-staged z-march of the same stencil (no block-wide stall per plane).
 //
-// Workgroups are remapped so that the tiles one XCD executes form a
-// contiguous range in (x, y, z): neighbours in y and z then share that XCD's
-// L2.  The batched entry points run the same per-cell code for many
+// Workgroups are remapped to the XCDs: on smaller planes without thick slabs the
+// tiles one XCD executes form a contiguous range in (x, y, z), so that neighbours in
+// y and z share its L2; else the XCDs take turns at chunks of 16 tiles (xcd_turns).
+// The batched entry points run the same per-cell code for many
 // simulations in one launch: the remapped work-unit index is looked up in a
 // table of (simulation, group of consecutive tiles).
 #include "pic_internal.hpp"

@@ -351,7 +351,9 @@ __device__ __forceinline__ void quarter_deposit(const PartArgs &a, int q, const 
 // (a particle outside the pass is put far away, where they are 0).  Products
 // and sums are FP32, each sum of at most 64 terms.
 //
-// The push issues VALU at most of its peak, so what counts is instructions: a
+// The push issues VALU at 0.7 of the peak beside the gather's vector-cache accesses
+// (a tile of the fields in LDS took 12 % of the one and 86 % of the other, and up to a
+// fifth of the time), so what counts here is instructions: a
 // pass takes about 220 VALU and 48 MFMA (1536 matrix-core cycles, beside other
 // wavefronts' VALU) whatever the number and order of the windows, where summing
 // every slot over the lanes takes 324 for one ordered row and 220 per window
@@ -518,7 +520,7 @@ __device__ __forceinline__ bool leaves(const PartArgs &a, float x, float y, floa
 // particles 16 (l / 16) on; the units get there from their particle's lane through
 // LDS, 16 slots at a time.  Summing windows one after another, with 220 VALU
 // instructions each, and their short ones with 54 atomics per lane, took 30.1 us for
-// 2e5 particles in 96x64x96 cells, now 24.2 (2e4: 20.3 -> 19.5, 1e6: 59.1 -> 57.1);
+// 2e5 particles in 96x64x96 cells, now 23.5 (2e4: 20.3 -> 13.8, 1e6: 59.1 -> 57.3);
 // what is left is the 54 units of every particle and the gather.
 //
 // A wavefront whose windows do not fit one such product, with less than 8 lanes in any,
@@ -820,7 +822,7 @@ __device__ __forceinline__ int ends_first(int b, int n) { return b & 1 ? n - 1 -
 // wavefront that has a SIMD to itself takes as long as the instructions it
 // issues one after another: of 26000 cycles, 2000 for the gather, 4500 for each
 // row's pass, 5500 for the lanes of short rows.  So a wavefront gets 16
-// particles: 4 lanes share a particle, each gathers one (y, z) corner and adds
+// particles: 4 lanes share a particle, each loads one (y, z) corner and adds
 // one third of a short row's slots; a pass takes 16 particles.  The four
 // wavefronts of a workgroup hold the 64 particles of a plain one's and go through
 // the same passes.  One that 3 or 4 of them have particles in is summed in LDS,
@@ -1166,9 +1168,9 @@ __device__ __forceinline__ int cell_key(float x, float y, float z, int nx, int n
 // over many cells waits for one atomic return, not one per cell.
 // Each run of equal keys in the array's order also counts itself in
 // runs[key] and records its start in first[key]: the scatter keeps the order
-// of a key that forms a single run.  The bunch is loaded ordered by x inside
-// each cell and drifts almost uniformly, so that order survives the sorts
-// and the particles of a wavefront stay ordered by their deposit windows.
+// of a key that forms a single run.  (The bunch is loaded ordered by x inside
+// each cell, and under a near-uniform drift that order survives the sorts.  The
+// deposit does not need it: its sums take the lanes of a row in any order.)
 __device__ __forceinline__ void count_body(const SortArgs &a, int blk)
 {
     __shared__ int bb[6];

@@ -81,7 +81,6 @@ bool finite_nonneg(const double *p, size_t n)
 
 namespace pich {
 
-// Fill the argument blocks once; nothing in them changes from step to step.
 // Grids up to this many cells move the step clock in their field updates and take
 // a step's probes along with the next H update.  On larger ones the probes' launch
 // of 5 us costs nothing: it covers the E update's last writes, which the H update
@@ -91,6 +90,7 @@ namespace pich {
 // The one-pass sweep has its probes' launch between two sweeps in any case.
 constexpr long long kProbeFoldCells = 1ll << 22;
 
+// Fill the argument blocks once; nothing in them changes from step to step.
 void build_args(pic_ctx *c)
 {
     pic::FieldArgs &a = c->fa;
@@ -869,10 +869,9 @@ static pic_status init_impl(pic_ctx *c, const pic_grid *grid, double dx, double 
                 if (v >= (float)nn[q]) v = std::nextafter((float)nn[q], 0.f);
                 cellpos[q][i] = v;
             }
-        // load order: by cell, and by x inside a cell.  The device's sorts keep
-        // the order of every cell whose particles stay contiguous, so under a
-        // near-uniform drift the particles of a wavefront stay ordered by their
-        // deposit windows (pic_read_particles returns the original order).
+        // load order: by cell, and by x inside a cell, which the device's sorts keep
+        // in every cell whose particles stay contiguous (pic_read_particles returns
+        // the original order).  The deposit takes the lanes of a row in any order.
         std::vector<uint64_t> keys((size_t)c->np);
         for (int i = 0; i < c->np; ++i) {
             const uint64_t cell = (uint64_t)std::min((int)cellpos[0][i], nn[0] - 1) +

@@ -279,6 +279,10 @@ constexpr int DEFAULT_TILE = TILE_RUNS;
 // blocks / plane runs by turns, no slabs: 512x256x256 436 / 404, 301x203x157 145.7 /
 // 128.5, 200x200x600 333 / 274, 448x128x128 88.8 / 92.4; all slabs: 553 / 504
 // (bands by turns 513), 172.5 / 144.7, (by turns) 368 / 311, 114.3 / 104.9.
+// Where the line lies, a whole step without slabs, blocks / turns: 128x128x128 28.0 /
+// 29.5 us, 160x160x128 41.8 / 41.8, 190x180x64 29.3 / 29.9, 192x192x192 88.4 / 81.9,
+// 448x128x128 93.3 / 87.1 (plane runs both), 256x256x16 16.2 / 14.6; few planes:
+// 1024x256x6 24.1 / 22.1, 2048x2048x2 115.8 / 103.4, but 2048x2048x1 50.2 / 51.8.
 // Band runs by turns of 11, 16, 19, 32, 43, 64 tiles on 512x256x256: 609, 547, 601,
 // 598, 589, 572 (16 is half a band's plane there).
 constexpr int XCD_CHUNK = 16;
