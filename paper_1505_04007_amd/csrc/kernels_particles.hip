@@ -650,21 +650,28 @@ __device__ __forceinline__ void deposit_fixed(const PartArgs &a, FixLds &L, unsi
 
 // A row of which a wavefront holds half its lanes or more lies in the dense part of the
 // bunch, where most wavefronts add to the same few cache lines and per-lane atomics on
-// one address follow each other at 17 ns: there the rows beside it (the particles that
-// moved back over a cell's face) are passes from DENSE_LANES lanes on.  Particles moving
-// every way, without / with: 2e5 in 180 cells 358 / 146 us, 1e6 in 4000 cells 590 / 241,
-// 2e5 with 15 % transverse velocities 134 / 71 (from 3 lanes on 93, from 5 on 126); in
-// beams sorted by row there are none (film 1e6, grating 1e7, batch: within 0.4 %).
+// one address follow each other at 17 ns: there the lanes between its own (of its
+// cells, in sorted order: particles that moved back over a face) are passes from
+// DENSE_LANES on.  Particles moving every way, without / with: 2e5 in 180 cells 358 /
+// 153 us, 1e6 in 4000 cells 590 / 337, 2e5 with 15 % transverse velocities 134 / 72
+// (from 3 lanes on 93, from 5 on 126).  The short rows before and after, a cold beam's
+// next ones, stay lane by lane: as passes 1e5 in 128x64x64 cells took 15.3 us for 14.2,
+// a batch of 16 118 for 116.
 constexpr int DENSE_LANES = 2;
+
+// The lanes from the first of m != 0 to the last.
+__device__ __forceinline__ unsigned long long between(unsigned long long m)
+{
+    return (~0ull >> __clzll((long long)m)) & (~0ull << (__ffsll((long long)m) - 1));
+}
 
 // The passes of a wavefront's rows; the lanes left over.
 __device__ __forceinline__ unsigned long long row_passes(const PartArgs &a, RowLds &L, unsigned long long rem,
                                                          int lane, const int base[3], float x0, float x1, bool yz)
 {
     const int lanes = __popcll(rem);
+    unsigned long long small = 0, widest = 0;
     for (int least = ROW_LANES;; least = DENSE_LANES) {
-        unsigned long long small = 0;
-        int most = 0;
         while (rem) {
             const int leader = __ffsll((long long)rem) - 1;
             // a lane behind the leader by less than a cell still joins its pass
@@ -674,12 +681,16 @@ __device__ __forceinline__ unsigned long long row_passes(const PartArgs &a, RowL
             const unsigned long long m =
                 __ballot(base[1] == by && base[2] == bz && (unsigned)(base[0] - X0) < (unsigned)ROW_BASES) & rem;
             rem &= ~m;
-            most = max(most, (int)__popcll(m));
-            if (__popcll(m) < least) small |= m;
-            else deposit_rows(a, L, m, lane, x0, x1, X0, by, bz, yz);
+            if (__popcll(m) < least) {
+                small |= m;
+                continue;
+            }
+            if (__popcll(m) > __popcll(widest)) widest = m;
+            deposit_rows(a, L, m, lane, x0, x1, X0, by, bz, yz);
         }
-        if (least != ROW_LANES || 2 * most < lanes || !small) return small;
-        rem = small;
+        if (least != ROW_LANES || !widest || 2 * __popcll(widest) < lanes) return small;
+        rem = small & between(widest);
+        small &= ~rem;
     }
 }
 
@@ -840,10 +851,8 @@ constexpr int SPLIT_MAX = 1 << 16;
 // not depend on their number (2e4 particles, least number 4, 7, 10, 16: 13.4,
 // 11.3, 9.8, 8.6 us; 1000: 9.5, 9.0, 8.4, 7.8).
 constexpr int SPLIT_LANES = 16;
-// But in the dense part of a bunch of more than SPLIT_DENSE (as for DENSE_LANES above),
-// the particles that lie, in sorted order, between those of the widest row form passes
-// from SPLIT_DENSE_LANES on: they are of its cells, where a neighbouring row of a cold
-// beam lies before or after.  Particles moving every way, without / with: 6000 in one
+// But in the dense part of a bunch of more than SPLIT_DENSE, the particles between the
+// widest row's form passes from SPLIT_DENSE_LANES on (as for DENSE_LANES above).  Particles moving every way, without / with: 6000 in one
 // cell 28.6 / 17.5 us, 2e4 in 180 cells 45 / 27, 65536 130 / 68; fewer than 4096 in one
 // cell lose as much to the passes' latency as they gain (2000: 14.3 / 14.8).
 constexpr int SPLIT_DENSE = 4096;
