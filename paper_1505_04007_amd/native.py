@@ -168,16 +168,16 @@ def to_compact(arr_xyz):
     if a.dtype == np.float64 and a.flags.c_contiguous:
         return a
     # A row reads one value from every x plane.  Where the planes' distance is a
-    # multiple of 2 KB, or a row has 1024 of them and more, the lines read do not stay
-    # in the cache for the next rows, so x goes in steps: 16 planes, of small planes as
-    # many as 256 KB hold (or the steps themselves take the time).  Whole rows / steps:
-    # 128x64x64 2.9 / 1.1 ms, 2048x17x16 3.3 / 1.2, 2^20 x 2 x 2 10 / 8; but 200x100x100
-    # 5.1 / 10.1, 281x1x3601 1.5 / 2.3, 91x45x53 0.36 / 0.45.
+    # multiple of 512 bytes, or a row has 1024 of them and more, the lines read do not
+    # stay in the cache for the next rows, so x goes in steps: 16 planes, of small planes
+    # as many as 64 KB hold (or the steps themselves take the time).  Whole rows / steps:
+    # 128x64x64 0.94 / 0.49 ms, 448x128x128 97 / 25, 208x80x72 1.15 / 0.68, 2^20 x 2 x 2
+    # 4.7 / 3.4; but 200x100x100 1.4 / 2.3, 281x1x3601 0.28 / 0.43, 300x300x300 37 / 71.
     plane = a.shape[0] * a.shape[1]
-    if a.shape[2] < 1024 and plane % 256:
+    if a.shape[2] < 1024 and plane % 64:
         return _f64(a)
     out = np.empty(a.shape)
-    step = max(16, 32768 // max(1, plane))
+    step = max(16, 8192 // max(1, plane))
     for i in range(0, a.shape[2], step):
         out[:, :, i:i + step] = a[:, :, i:i + step]
     return out
