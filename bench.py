@@ -205,7 +205,7 @@ def run_batched(steps, warmup, tune_reps):
         del sim
     sims = [native.from_workload(w) for w in ws]
     batch = native.Batch(sims, use_graph=True)
-    tune = batch.tune(reps=tune_reps) if tune_reps > 0 else batch.tune(force=0)
+    tune = batch.tune(reps=tune_reps) if tune_reps > 0 else batch.tune(force=native.DEFAULT_TILE)
     batch.step(warmup)
     torch.cuda.synchronize()
     p0 = sum(s.stats()["pushes"] for s in sims)
@@ -405,7 +405,7 @@ def main():
         w.sort_every = args.sort_every
     sim = native.from_workload(w, timing=args.timing_every, deposit_mode=args.deposit_mode,
                                field_sweep=args.field_sweep)
-    tune = sim.tune(force=0) if args.no_tune else sim.tune(reps=10)
+    tune = sim.tune(force=native.DEFAULT_TILE) if args.no_tune else sim.tune(reps=10)
     if not args.no_tune:
         print("[bench] tile variants ms per H+E pair: " + " ".join(f"{m:.3f}" for m in tune["ms"]),
               file=sys.stderr, flush=True)

@@ -78,8 +78,13 @@ EXPORTS = ("pic_abi_version", "pic_init", "pic_step", "pic_probe", "pic_grad", "
            "pic_batch_destroy", "pic_batch_last_error", "pic_query_sizes", "pic_grad_noalloc")
 
 
+# the field kernels' tile shape before any tuning: runs of 256 cells, plane by plane
+DEFAULT_TILE = 3
+
+
 def _tune_dict(t):
     return {"tile": t.tile, "fx": t.fx, "fy": t.fy, "order": t.order, "ms": list(t.ms)[: t.nshapes]}
+
 
 _LIB = None
 
