@@ -473,16 +473,17 @@ void launch_e_update(const FieldArgs &a, hipStream_t s)
     launch_shape<ELaunch>(a.tile, field_tiles(a.nx, a.ny, a.nz, a.tile), s, a);
 }
 
-void launch_h_update_batch(const FieldArgs *args, const int *own, int total, int shape, const ProbeArgs *probe,
-                           int nmem, hipStream_t s)
+void launch_h_update_batch(const FieldArgs *args, const int *own, int total, int shape, bool turns,
+                           const ProbeArgs *probe, int nmem, hipStream_t s)
 {
     const int extra = (nmem + XCDS - 1) / XCDS * XCDS;
-    launch_shape<HBatchLaunch>(shape, total + extra, s, args, own, probe, nmem, extra, xcd_turns(total));
+    launch_shape<HBatchLaunch>(shape, total + extra, s, args, own, probe, nmem, extra,
+                               turns ? xcd_turns(total) : 0);
 }
 
-void launch_e_update_batch(const FieldArgs *args, const int *own, int total, int shape, hipStream_t s)
+void launch_e_update_batch(const FieldArgs *args, const int *own, int total, int shape, bool turns, hipStream_t s)
 {
-    launch_shape<EBatchLaunch>(shape, total, s, args, own, xcd_turns(total));
+    launch_shape<EBatchLaunch>(shape, total, s, args, own, turns ? xcd_turns(total) : 0);
 }
 
 }  // namespace pic

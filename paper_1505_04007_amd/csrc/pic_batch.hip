@@ -24,6 +24,7 @@ struct pic_batch {
     int push_mode = 0;  // bit 0: per-lane atomics, bit 1: some member has a periodic x axis
     int sort_every = 0;
     int tile = 0;       // field-kernel tile shape shared by all members (pic_batch_tune)
+    bool turns = false; // the XCDs take turns at the field launches' units with that shape
     bool particles = false;
     bool use_graph = false;
     bool stale = false;  // the device's blocks may not be those of `tile` (a tuner's failure left them so)
@@ -72,10 +73,11 @@ void batch_free(pic_batch *b)
 void batch_launches(pic_batch *b, bool first)
 {
     const int n = (int)b->ctx.size();
-    pic::launch_h_update_batch(b->d_fa, b->d_tiles, b->total_tiles, b->tile, first ? nullptr : b->d_pr, n, b->stream);
+    pic::launch_h_update_batch(b->d_fa, b->d_tiles, b->total_tiles, b->tile, b->turns,
+                               first ? nullptr : b->d_pr, n, b->stream);
     if (b->particles)
         pic::launch_push_deposit_batch(b->d_pa, b->d_pblocks, b->total_pblocks, b->push_mode, b->stream);
-    pic::launch_e_update_batch(b->d_fa, b->d_tiles, b->total_tiles, b->tile, b->stream);
+    pic::launch_e_update_batch(b->d_fa, b->d_tiles, b->total_tiles, b->tile, b->turns, b->stream);
 }
 
 void batch_probe(pic_batch *b) { pic::launch_probe_batch(b->d_pr, (int)b->ctx.size(), b->stream); }
@@ -127,11 +129,14 @@ pic_status batch_upload_fields(pic_batch *b, int shape, bool tick = true)
         tiles[q] = pic::batch_field_units(c->n[0], c->n[1], c->n[2], shape);
         if (tiles[q] >= (1LL << 24)) return bfail(b, PIC_EINVAL, "member %d has too many field tiles for a batch", q);
     }
+    bool turns = false;
+    for (const pic::FieldArgs &a : fa) turns = turns || pic::turns_pay(a);
     const std::vector<int> tab = unit_table(tiles);
     if (tab.size() > b->tiles_cap) return bfail(b, PIC_EINVAL, "field tile table larger than allocated");
     BHIP(b, hipMemcpy(b->d_fa, fa.data(), sizeof(pic::FieldArgs) * n, hipMemcpyHostToDevice));
     BHIP(b, hipMemcpy(b->d_tiles, tab.data(), sizeof(int) * tab.size(), hipMemcpyHostToDevice));
     b->tile = shape;
+    b->turns = turns;
     b->total_tiles = (int)tab.size();
     return PIC_OK;
 }
@@ -350,12 +355,19 @@ pic_status pic_batch_tune(pic_batch *b, int32_t reps, int32_t force, pic_tune_ou
         for (int v = 0; v < pic::N_TILE_SHAPES && st == PIC_OK; ++v) {
             st = batch_upload_fields(b, v, false);  // the clock stands still while launches are timed
             if (st != PIC_OK) break;
-            pic::launch_h_update_batch(b->d_fa, b->d_tiles, b->total_tiles, v, nullptr, (int)b->ctx.size(), b->stream);
-            pic::launch_e_update_batch(b->d_fa, b->d_tiles, b->total_tiles, v, b->stream);
+            const auto launch_h = [&] {
+                pic::launch_h_update_batch(b->d_fa, b->d_tiles, b->total_tiles, v, b->turns, nullptr,
+                                           (int)b->ctx.size(), b->stream);
+            };
+            const auto launch_e = [&] {
+                pic::launch_e_update_batch(b->d_fa, b->d_tiles, b->total_tiles, v, b->turns, b->stream);
+            };
+            launch_h();
+            launch_e();
             (void)hipEventRecord(e0, b->stream);
             for (int r = 0; r < reps; ++r) {
-                pic::launch_h_update_batch(b->d_fa, b->d_tiles, b->total_tiles, v, nullptr, (int)b->ctx.size(), b->stream);
-                pic::launch_e_update_batch(b->d_fa, b->d_tiles, b->total_tiles, v, b->stream);
+                launch_h();
+                launch_e();
             }
             (void)hipEventRecord(e1, b->stream);
             float t = 0.f;

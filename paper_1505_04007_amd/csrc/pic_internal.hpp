@@ -275,10 +275,12 @@ constexpr int DEFAULT_TILE = TILE_RUNS;
 // H + E pair and adjoint pair, blocks / turns, order by plane: a batch of 16 of
 // 176x64x64 and up 381 / 361 us, 128x64x64 15.3 / 15.2 and 26.0 / 21.8; but 281x1x3601
 // with slabs of 10 of 450 planes 19.0 / 20.8, 96x64x96 without slabs 17.2 / 17.8,
-// 91x45x53 (848 tiles) 10.0 / 10.2 and 12.4 / 12.6.  Large planes, band runs in
-// blocks / plane runs by turns, no slabs: 512x256x256 436 / 404, 301x203x157 145.7 /
-// 128.5, 200x200x600 333 / 274, 448x128x128 88.8 / 92.4; all slabs: 553 / 504
-// (bands by turns 513), 172.5 / 144.7, (by turns) 368 / 311, 114.3 / 104.9.
+// 91x45x53 (848 tiles) 10.0 / 10.2 and 12.4 / 12.6.  (A batch takes turns when they pay
+// for a member: 16 of 64x64x64 cells without slabs, a step, 62 / 70 us, of 128x64x64 113
+// / 133.)  Large planes, band runs in blocks / plane runs by turns, no slabs: 512x256x256
+// 436 / 404, 301x203x157 145.7 / 128.5, 200x200x600 333 / 274, 448x128x128 88.8 / 92.4;
+// all slabs: 553 / 504 (bands by turns 513), 172.5 / 144.7, (by turns) 368 / 311, 114.3
+// / 104.9.
 // Where the line lies, a whole step without slabs, blocks / turns: 128x128x128 28.0 /
 // 29.5 us, 160x160x128 41.8 / 41.8, 190x180x64 29.3 / 29.9, 192x192x192 88.4 / 81.9,
 // 448x128x128 93.3 / 87.1 (plane runs both), 256x256x16 16.2 / 14.6; few planes:
@@ -287,9 +289,20 @@ constexpr int DEFAULT_TILE = TILE_RUNS;
 // 598, 589, 572 (16 is half a band's plane there).
 constexpr int XCD_CHUNK = 16;
 inline int xcd_turns(long long tiles) { return (int)(tiles / (8 * XCD_CHUNK)) * XCD_CHUNK; }
+inline bool turns_pay(long long plane, int n, const PmlAxis &slow)
+{
+    return plane > (1 << 15) || (slow.on && 32LL * slow.npml >= n);
+}
 inline int xcd_turns(long long tiles, long long plane, int n, const PmlAxis &slow)
 {
-    return tiles >= 1024 && (plane > (1 << 15) || (slow.on && 32LL * slow.npml >= n)) ? xcd_turns(tiles) : 0;
+    return tiles >= 1024 && turns_pay(plane, n, slow) ? xcd_turns(tiles) : 0;
+}
+
+// The same for a's grid in the order of its tile shape.
+inline bool turns_pay(const FieldArgs &a)
+{
+    const int slow = TILE_ZO[a.tile] ? 1 : 2;
+    return turns_pay(slow == 1 ? 0 : (long long)a.nx * a.ny, slow == 1 ? a.ny : a.nz, a.pml[slow]);
 }
 
 // (a's sizes and slabs are set)
@@ -301,9 +314,8 @@ inline void set_tile(FieldArgs &a, int shape)
     a.dx = make_div(runs || band ? a.nx : a.gx);
     a.dy = make_div(runs ? a.ny : band ? a.gx : a.gy);
     a.dz = make_div(a.nz);
-    const int slow = TILE_ZO[shape] ? 1 : 2;
-    a.turns = xcd_turns(field_tiles(a.nx, a.ny, a.nz, shape), slow == 1 ? 0 : (long long)a.nx * a.ny,
-                        slow == 1 ? a.ny : a.nz, a.pml[slow]);
+    const int tiles = field_tiles(a.nx, a.ny, a.nz, shape);
+    a.turns = tiles >= 1024 && turns_pay(a) ? xcd_turns(tiles) : 0;
 }
 
 // Work units of one member in a batched field launch.
@@ -428,9 +440,11 @@ int scan_tmp_size(long long n);
 // of per-simulation argument blocks; `own` a device table with one entry per
 // work unit of the launch (field tile / particle workgroup, `total` of them):
 // simulation index << 24 | the unit's index within that simulation.
-void launch_h_update_batch(const FieldArgs *args, const int *own, int total, int shape, const ProbeArgs *probe,
-                           int nmem, hipStream_t s);
-void launch_e_update_batch(const FieldArgs *args, const int *own, int total, int shape, hipStream_t s);
+// turns: the XCDs take turns at the units (xcd_turns), which a batch does when it pays
+// for one of its members.
+void launch_h_update_batch(const FieldArgs *args, const int *own, int total, int shape, bool turns,
+                           const ProbeArgs *probe, int nmem, hipStream_t s);
+void launch_e_update_batch(const FieldArgs *args, const int *own, int total, int shape, bool turns, hipStream_t s);
 void launch_push_deposit_batch(const PartArgs *args, const int *own, int total, int mode, hipStream_t s);
 void launch_probe_batch(const ProbeArgs *args, int n, hipStream_t s);
 
