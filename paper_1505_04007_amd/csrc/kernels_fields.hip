@@ -319,13 +319,15 @@ __device__ __forceinline__ bool first_thread() { return threadIdx.x == 0 && thre
 // Workgroups in front of an H update's tiles: the first (of each simulation of a
 // batch) passes the step's clock to the E update and, with pr.nprobe > 0, takes
 // the probes of the step before; a whole round of the XCDs, so that the tiles
-// keep theirs.
+// keep theirs.  LARGE: with large phases (a batch's members may have them; a
+// simulation of its own that may takes its probes by a launch).
 constexpr int XCDS = 8;
 
+template <int LARGE>
 __device__ __forceinline__ void h_front(const ProbeArgs &pr, DevState *state, int t, int nt)
 {
     const gp<DevState> st = G(state);
-    if (pr.nprobe > 0) probe_dft(pr, st->step, t, nt);
+    if (pr.nprobe > 0) probe_dft<LARGE>(pr, st->step, t, nt);
     if (t == 0) {
         st->e_parity = st->parity;
         st->e_since = st->since_sort;
@@ -340,7 +342,7 @@ __global__ __launch_bounds__(TXW *TYW) void k_h_update(FieldArgs a, ProbeArgs pr
 {
     const int blk = (int)blockIdx.x - FRONT;
     if (FRONT && blk < 0) {
-        if (blockIdx.x == 0) h_front(pr, a.st, threadIdx.x + TXW * threadIdx.y, TXW * TYW);
+        if (blockIdx.x == 0) h_front<0>(pr, a.st, threadIdx.x + TXW * threadIdx.y, TXW * TYW);
         return;
     }
     int i, j, k;
@@ -373,7 +375,7 @@ __global__ __launch_bounds__(TXW *TYW) void k_h_update_batch(const FieldArgs *__
     const int blk = (int)blockIdx.x - extra;
     if (blk < 0) {
         const int m = blockIdx.x, t = threadIdx.x + TXW * threadIdx.y;
-        if (m < nmem) h_front(probe ? probe[m] : ProbeArgs{}, args[m].st, t, TXW * TYW);
+        if (m < nmem) h_front<1>(probe ? probe[m] : ProbeArgs{}, args[m].st, t, TXW * TYW);
         return;
     }
     const int o = own[xcd_tile(blk, gridDim.x - extra, turns)];

@@ -87,7 +87,8 @@ namespace pich {
 // would wait for, and an H update whose launch writes the clock is slower (512x
 // 256x256 cells: 276 us, otherwise 265; 448x128x128: a step of 187.1 us, otherwise
 // 186.7; 160x160x128: 68.8, otherwise 69.7; 281x1x3601: 35.4, otherwise 42.3).
-// The one-pass sweep has its probes' launch between two sweeps in any case.
+// The one-pass sweep has its probes' launch between two sweeps in any case, and so do
+// probes with phases that may be large (ProbeArgs::large).
 constexpr long long kProbeFoldCells = 1ll << 22;
 
 // Fill the argument blocks once; nothing in them changes from step to step.
@@ -117,7 +118,7 @@ void build_args(pic_ctx *c)
     a.coef = c->coef;
     a.pbox = c->np > 0 ? c->box : nullptr;
     a.nan_flag = c->d_nan;
-    a.tick = !c->fused && (long long)c->n[0] * c->n[1] * c->n[2] <= kProbeFoldCells;
+    a.tick = !c->fused && !c->large_phases && (long long)c->n[0] * c->n[1] * c->n[2] <= kProbeFoldCells;
     a.st = c->dstate;
 
     pic::PartArgs &pa = c->pa;
@@ -167,6 +168,7 @@ void build_args(pic_ctx *c)
     pr.nfreq = c->nfreq;
     pr.pidx = c->pidx;
     pr.omega = c->omega;
+    pr.large = c->large_phases;
     pr.fre = c->fre;
     pr.fim = c->fim;
     pr.series = c->series;
@@ -840,6 +842,7 @@ static pic_status init_impl(pic_ctx *c, const pic_grid *grid, double dx, double 
         TRY(dalloc(c, &c->omega, c->nfreq > 0 ? c->nfreq : 1));
         TRY(dalloc(c, &c->fre, nf ? nf : 1));
         TRY(dalloc(c, &c->fim, nf ? nf : 1));
+        for (int f = 0; f < c->nfreq; ++f) c->large_phases |= !(std::fabs(o.omega[f]) * dt < 4.0);
         if (c->nfreq > 0)
             HIP_TRY(c, hipMemcpyAsync(c->omega, o.omega, 8 * (size_t)c->nfreq, hipMemcpyHostToDevice, c->stream));
         HIP_TRY(c, hipMemsetAsync(c->fre, 0, 8 * (nf ? nf : 1), c->stream));

@@ -74,6 +74,7 @@ struct pic_ctx {
 
     int nprobe = 0, nfreq = 0;
     int *pidx = nullptr;
+    bool large_phases = false;  // ProbeArgs::large
     double *omega = nullptr, *fre = nullptr, *fim = nullptr;
     float *series = nullptr;
     long long series_len = 0;

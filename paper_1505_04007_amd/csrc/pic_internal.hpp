@@ -214,6 +214,7 @@ struct ProbeArgs {
     int nprobe, nfreq;
     const int *pidx;      // linear Ez index per probe
     const double *omega;  // rad/s
+    int large;            // some |omega| dt is 4 or more: below, no phase comes near 2^45
     double *fre, *fim;
     float *series;        // [series_len * nprobe] or null
     long long series_len;
@@ -556,17 +557,21 @@ __device__ __forceinline__ double reduce_large(double x, int &q)
     return x < 0.0 ? -r : r;
 }
 
-// sin and cos of x: x less the nearest multiple n of pi/2, then the Taylor series on
-// [-pi/4, pi/4] (the first terms left out are below 1e-19).  Up to 2^45 pi/2 is a sum
-// of two doubles, each product exact in the fma (n times what they leave out of pi/2
-// is below 4e-20).  The library function's code would take the field kernel that
-// carries the probes to twice its registers.
-__device__ __forceinline__ void sincos_phase(double x, double &sn, double &cs)
+// |x| < 2^45 less the nearest multiple n of pi/2, and n mod 4: pi/2 as a sum of two
+// doubles, each product exact in the fma (n times what they leave out of pi/2 is below
+// 4e-20).
+__device__ __forceinline__ double reduce_phase(double x, int &q)
 {
     const double n = rint(x * 0.63661977236758134308);
-    double r = fma(-n, 6.123233995736766036e-17, fma(-n, 1.5707963267948965580, x));
-    int q = (int)(n - 4.0 * floor(0.25 * n));
-    if (__builtin_expect(!(fabs(x) < 0x1p45), 0)) r = reduce_large(x, q);
+    q = (int)(n - 4.0 * floor(0.25 * n));
+    return fma(-n, 6.123233995736766036e-17, fma(-n, 1.5707963267948965580, x));
+}
+
+// sin and cos of r + q pi/2 by the Taylor series on [-pi/4, pi/4] (the first terms left
+// out are below 1e-19).  The library functions would take the field kernel that carries
+// the probes to twice its registers.
+__device__ __forceinline__ void sincos_reduced(double r, int q, double &sn, double &cs)
+{
     const double z = r * r;
     double s = -1.0 / 121645100408832000.0, c = -1.0 / 6402373705728000.0;  // -1/19!, -1/18!
     s = fma(s, z, 1.0 / 355687428096000.0);
@@ -595,6 +600,8 @@ __device__ __forceinline__ void sincos_phase(double x, double &sn, double &cs)
 // F_p(w_m) += dt Ez_p^n exp(-i w_m n dt) for the newest field E^n, n = n1 steps
 // taken (Sec. IV, Figs. 6-7: Ez at the film surface and its spectrum), by one
 // workgroup of nt threads; the phase is evaluated directly in FP64 each step.
+// LARGE: phases may be 2^45 or more (ProbeArgs::large).
+template <int LARGE>
 __device__ __forceinline__ void probe_dft(const ProbeArgs &a, long long n1, int t, int nt)
 {
     const gp<const float> Ez = G(a.Ez);
@@ -602,9 +609,11 @@ __device__ __forceinline__ void probe_dft(const ProbeArgs &a, long long n1, int 
     const double tn = (double)n1 * a.dt;
     for (int q = t; q < a.nprobe * a.nfreq; q += nt) {
         const int p = q / a.nfreq, f = q - p * a.nfreq;
-        const double ez = (double)Ez[pidx[p]];
-        double sn, cs;
-        sincos_phase(G(a.omega)[f] * tn, sn, cs);
+        const double ez = (double)Ez[pidx[p]], x = G(a.omega)[f] * tn;
+        int k;
+        double sn, cs, r = reduce_phase(x, k);
+        if (LARGE && !(fabs(x) < 0x1p45)) r = reduce_large(x, k);
+        sincos_reduced(r, k, sn, cs);
         G(a.fre)[q] += a.dt * ez * cs;
         G(a.fim)[q] -= a.dt * ez * sn;
     }

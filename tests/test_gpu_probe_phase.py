@@ -21,13 +21,17 @@ OMEGA = np.concatenate([np.array([0.0, 0.3, -1.7, 1e3, 1e9, 2.0 ** 30, 1e15, -1e
                         [EDGE, np.nextafter(EDGE, 0), np.nextafter(EDGE, np.inf), -EDGE]])
 
 
+BELOW = np.array([0.0, 1e-3, -2.5, np.nextafter(4.0, 0)]) / DT  # all of a step's phase below 4: no large ones
+
+
+@pytest.mark.parametrize("omega", [OMEGA, BELOW, np.append(BELOW, 4.0 / DT)])
 @pytest.mark.parametrize("how", ["one call", "step by step", "batch", "one sweep"])
-def test_spectra_at_any_phase(how):
+def test_spectra_at_any_phase(how, omega):
     rng = np.random.default_rng(3)
     E = [rng.standard_normal(N) for _ in range(3)]
     z = np.zeros(N)
     probes = np.array([[4.5, 4.5, 4.5], [7.0, 2.0, 3.0], [2.0, 6.0, 5.0]]) * DX
-    s = native.Simulation(*N, DX, DT, z, z, probes=probes, omega=OMEGA, series_len=STEPS, init_E=E,
+    s = native.Simulation(*N, DX, DT, z, z, probes=probes, omega=omega, series_len=STEPS, init_E=E,
                           field_sweep=int(how == "one sweep"))
     if how == "batch":
         native.Batch([s]).step(STEPS)
@@ -41,7 +45,7 @@ def test_spectra_at_any_phase(how):
     assert np.abs(ser).max() > 0
     for p in range(len(probes)):
         bound = 1e-15 * np.sum(np.abs(ser[:, p])) * DT
-        for m, w in enumerate(OMEGA):
+        for m, w in enumerate(omega):
             ph = [float(w) * (n * DT) for n in range(1, STEPS + 1)]
             re = math.fsum(DT * ser[n, p] * math.cos(ph[n]) for n in range(STEPS))
             im = math.fsum(-DT * ser[n, p] * math.sin(ph[n]) for n in range(STEPS))
